@@ -365,17 +365,15 @@ hdc_status hdc_validate_offsets(const int64_t* offsets, int64_t num_segments,
  * how many small segments share one wavefront (power of two, 1..64, each
  * served by 64/seg_per_wave lanes).  For HDC_OP_SCAN, block sets the tile
  * (block * 16 elements) and unroll 1 selects the three-pass schedule.
- * passes, 1 or 2 (default 2).  HDC_OP_TRANSFORM_REDUCE, HDC_OP_DOT,
- * HDC_OP_MAP_REDUCE: 1 folds the per-block partials in the same launch, in
- * the block that arrives last on a ticket (library-owned device memory, one
- * per workspace buffer), if the grid's partials fit its LDS stage (32 KiB),
- * else in a second launch; 2 always folds them in a second launch.  Both
- * fold in the same order, so `passes` does not change any result bit.  (A
- * one-launch fold whose wait for a partial gave up -- not expected -- writes
- * NaN, or INT64_MIN for int64 sums.)  The exact bf16 sum and the exact fp16
- * dot always use two launches.  HDC_OP_SEGMENTED_REDUCE: 1 selects the tiled
- * schedule (fixed tiles of `chunk` elements, no plan), 2 the planned one
- * (pieces of `chunk`, packed small segments).  Tuning changes
+ * passes, 1 or 2 (default 2; 1 for the reductions of buckets 0..2).
+ * HDC_OP_TRANSFORM_REDUCE, HDC_OP_DOT, HDC_OP_MAP_REDUCE: 1 folds the
+ * per-block partials in the same launch, in the block that arrives last on a
+ * ticket (library-owned device memory, one per workspace buffer and stream; a
+ * call that finds none left takes two launches); 2 folds them in a second
+ * launch (none when the grid is one block).  Both fold in the same order, so
+ * `passes` does not change any result bit.  HDC_OP_SEGMENTED_REDUCE: 1
+ * selects the tiled schedule (fixed tiles of `chunk` elements, no plan), 2
+ * the planned one (pieces of `chunk`, packed small segments).  Tuning changes
  * the summation order, so the last bits of a floating-point sum may change;
  * results stay within the stated tolerance. */
 typedef struct hdc_tuning {

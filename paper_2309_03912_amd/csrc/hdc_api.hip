@@ -15,7 +15,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
-#include <unordered_map>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -200,6 +199,17 @@ void ensure_tuning_loaded() {
     for (auto& per_dt : g_tune[HDC_OP_BATCH])
       for (auto& per_acc : per_dt)
         for (Tuning& t : per_acc) t.chunk = 32768;
+    // Reductions of fewer than 2^24 elements fold their partials in the same
+    // launch: on the GPU the two forms are within ~1 us of each other, but a
+    // launch costs the host ~4 us, so two of them made a stream of small
+    // calls run at 12.1 us a call against 8.5 us.  From 2^24 elements on the
+    // kernel outlasts both launches and the two forms are within 1-3% either
+    // way (2^24 bf16: 11.1 against 10.0 us; 2^28 f32: 155.0 against 155.2 us),
+    // so the cache decides.
+    for (int op : {HDC_OP_TRANSFORM_REDUCE, HDC_OP_DOT, HDC_OP_MAP_REDUCE})
+      for (auto& per_dt : g_tune[op])
+        for (auto& per_acc : per_dt)
+          for (int b = 0; b < 3; ++b) per_acc[b].passes = 1;
     const char* p = getenv("HDC_TUNE_CACHE");
     if (p && *p) {
       if (!tune_cache_on()) {
@@ -306,28 +316,28 @@ hdc_status scratch_address(void** out) {
 // Tickets of the one-launch reductions
 // ---------------------------------------------------------------------------
 
-// A one-launch reduction counts its finished blocks on a ticket (a launch
-// epoch and an arrival count) whose count must be 0 when the kernel starts;
-// the block that arrives last folds the partials and moves the ticket to the
-// next epoch with a count of 0.  The tickets are library-owned device memory
-// (an object of static storage, so zero-initialized when the code object is
-// loaded), one per workspace buffer: calls that share a workspace are ordered
-// on one stream, so they never use one ticket at the same time, while calls
-// on different workspaces never share one.  Once every slot of a device is
-// taken, calls with new workspace buffers use the two-launch form.
-constexpr int kTicketSlots = 1 << 16;
-static __device__ uint64_t tickets[kTicketSlots];
+// A one-launch reduction counts its finished blocks on a ticket (kTicketWords
+// counters) that must be 0 when the kernel starts; the kernel leaves it 0.
+// The tickets are library-owned device memory (an object of static storage,
+// so zero-initialized when the code object is loaded), one per workspace
+// buffer and stream: calls on one stream are ordered, so they never use a
+// ticket at the same time, and calls that wrongly share a workspace across
+// streams can spoil each other's partials but not a ticket, which later calls
+// rely on.  Once every slot of a device is taken, calls with a new workspace
+// or stream use the two-launch form.
+constexpr int kTicketSlots = 1 << 11;  // 4352 bytes each
+static __device__ __align__(256) uint32_t tickets[(size_t)kTicketSlots * kTicketWords];
 
 struct TicketTable {
-  uint64_t* base = nullptr;  // device address of `tickets` on this device
-  std::unordered_map<const void*, int> slot;
+  uint32_t* base = nullptr;  // device address of `tickets` on this device
+  std::map<std::pair<const void*, hipStream_t>, int> slot;
 };
 std::mutex g_ticket_mu;
 TicketTable g_ticket_tables[kMaxDevices];
 
-// The ticket of workspace buffer `ws` on the current device, or NULL when
-// no slot is left.
-hdc_status ticket_for(const void* ws, uint64_t** out) {
+// The ticket of workspace buffer `ws` and stream `st` on the current device,
+// or NULL when no slot is left.
+hdc_status ticket_for(const void* ws, hipStream_t st, uint32_t** out) {
   *out = nullptr;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -339,14 +349,15 @@ hdc_status ticket_for(const void* ws, uint64_t** out) {
     void* p = nullptr;
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(tickets));
     if (e != hipSuccess || !p) return fail(HDC_ERR_HIP, "hipGetSymbolAddress(tickets): %s", hipGetErrorString(e));
-    tt.base = static_cast<uint64_t*>(p);
+    tt.base = static_cast<uint32_t*>(p);
   }
-  auto it = tt.slot.find(ws);
+  const std::pair<const void*, hipStream_t> key{ws, st};
+  auto it = tt.slot.find(key);
   if (it == tt.slot.end()) {
     if (tt.slot.size() >= (size_t)kTicketSlots) return HDC_OK;
-    it = tt.slot.emplace(ws, (int)tt.slot.size()).first;
+    it = tt.slot.emplace(key, (int)tt.slot.size()).first;
   }
-  *out = tt.base + it->second;
+  *out = tt.base + (size_t)it->second * kTicketWords;
   return HDC_OK;
 }
 
@@ -471,13 +482,11 @@ static hdc_status reduce_common(const hdc_functor* f, const hdc_functor* fm, hdc
   }
   const int op = fused ? HDC_OP_MAP_REDUCE : f->id == HDC_FN_PRODUCT ? HDC_OP_DOT : HDC_OP_TRANSFORM_REDUCE;
   const Tuning t = tuning_for(op, dt, acc, n);
-  uint64_t* ticket = nullptr;
-  if (t.passes == 1) HDC_TRY(ticket_for(ws, &ticket));
+  uint32_t* ticket = nullptr;
+  if (t.passes == 1) HDC_TRY(ticket_for(ws, st, &ticket));
   if (log_on()) {
-    const bool own = acc == HDC_ACC_EXACT && !fused && (f->id == HDC_FN_PRODUCT || dt == HDC_BF16);
     log_dispatch(fused ? "map_reduce" : f->id == HDC_FN_PRODUCT ? "dot" : "transform_reduce", dt, acc, n, t,
-                 own ? "exact kernel and its final fold (two launches)"
-                     : t.passes == 1 ? "one launch (the last block folds the partials)" : "two launches",
+                 ticket ? "one launch (the last block folds the partials)" : "two launches",
                  noalloc ? "static scratch" : workspace ? "caller" : "library");
   }
 

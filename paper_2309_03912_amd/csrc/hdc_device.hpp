@@ -97,6 +97,15 @@ struct IntAcc {
   __host__ __device__ static IntAcc merge(IntAcc a, IntAcc b) { return {a.s + b.s}; }
 };
 
+// (m + a fraction in (0, 1) if `rest`) * 2^e, with the top bit of m set, rounded
+// once to fp64 (nearest, ties to even).
+__host__ __device__ __forceinline__ double round_top64(uint64_t m, bool rest, int e) {
+  uint64_t k = m >> 11;  // 53 bits
+  const uint64_t low = m & 0x7FFu;
+  if (low > 0x400u || (low == 0x400u && (rest || (k & 1u)))) k += 1;  // k <= 2^53: exact as a double
+  return __builtin_ldexp((double)k, e + 11);
+}
+
 // Exact sum of fp16 values.  Every fp16 value is an integer multiple of 2^-24
 // below 2^16 in magnitude, so a chain of at most 2^13 of them summed in fp64
 // never rounds (each partial sum is a multiple of 2^-24 below 2^29: 53 bits).
@@ -145,26 +154,14 @@ struct ExactAcc {
       ml = ~ml + 1;
       mh = ~mh + (ml == 0 ? 1u : 0u);
     }
-    int top = -1;  // index of the highest set bit of the 128-bit magnitude
-    if (mh) top = 127 - __builtin_clzll(mh);
-    else if (ml) top = 63 - __builtin_clzll(ml);
-    if (top < 0) return 0.0;
-    double r;
-    if (top < 53) {
-      r = (double)ml;  // exact
-    } else {
-      const int sh = top - 52;  // drop the `sh` low bits, keep 53
-      auto bit = [&](int i) -> uint64_t { return i >= 64 ? (mh >> (i - 64)) & 1u : (ml >> i) & 1u; };
-      uint64_t m = 0;
-      for (int i = top; i >= sh; --i) m = (m << 1) | bit(i);
-      const uint64_t guard = bit(sh - 1);
-      uint64_t sticky = 0;
-      for (int i = sh - 2; i >= 0 && !sticky; --i) sticky = bit(i);
-      if (guard && (sticky || (m & 1u))) m += 1;
-      r = __builtin_ldexp((double)m, sh);  // m <= 2^53: exact
-    }
-    r = __builtin_ldexp(r, -24);
-    return neg ? -r : r;
+    if ((ml | mh) == 0) return 0.0;
+    // The 64 bits below and including the highest set bit, and whether any
+    // bit below them is set.
+    const int lz = mh ? __builtin_clzll(mh) : __builtin_clzll(ml);
+    const uint64_t m = !mh ? ml << lz : lz ? (mh << lz) | (ml >> (64 - lz)) : mh;
+    const bool rest = mh && (ml << lz) != 0;
+    const double r = round_top64(m, rest, mh ? 64 - lz : -lz);
+    return neg ? -__builtin_ldexp(r, -24) : __builtin_ldexp(r, -24);
   }
 };
 

@@ -80,27 +80,64 @@ struct Bf16Exact {
         g[j] = v;
       }
     }
-    int top = -1;  // highest set bit; bit 0 has the value 2^-134
-    for (int j = kExactDigits - 1; j >= 0 && top < 0; --j)
-      if (g[j]) top = 32 * j + 31 - __builtin_clz(g[j]);
-    if (top < 0) return 0.0;
-    auto bit = [&](int i) -> uint64_t { return (g[i >> 5] >> (i & 31)) & 1u; };
-    double r;
-    if (top < 53) {
-      r = __builtin_ldexp((double)((uint64_t)g[0] | ((uint64_t)g[1] << 32)), -134);  // exact
-    } else {
-      const int sh = top - 52;  // keep bits [sh, top]
-      uint64_t m = 0;
-      for (int i = top; i >= sh; --i) m = (m << 1) | bit(i);
-      const uint64_t guard = bit(sh - 1);
-      uint64_t sticky = 0;
-      for (int i = sh - 2; i >= 0 && !sticky; --i) sticky = bit(i);
-      if (guard && (sticky || (m & 1u))) m += 1;  // m <= 2^53: exact as a double
-      r = __builtin_ldexp((double)m, sh - 134);
+    // The highest non-zero digit and the two below it (constant indices: the
+    // digits stay in registers), and whether any lower digit is non-zero.
+    uint32_t h = 0, m1 = 0, m0 = 0;
+    int top = -1;
+    bool rest = false;
+#pragma unroll
+    for (int j = kExactDigits - 1; j >= 0; --j) {
+      if (top < 0) {
+        if (g[j]) {
+          top = j;
+          h = g[j];
+          m1 = j >= 1 ? g[j - 1] : 0;
+          m0 = j >= 2 ? g[j - 2] : 0;
+        }
+      } else if (j < top - 2) {
+        rest = rest || g[j] != 0;
+      }
     }
+    if (top < 0) return 0.0;
+    const int lz = __builtin_clz(h);
+    const uint64_t hi = ((uint64_t)h << 32) | m1;
+    const uint64_t m = (hi << lz) | (lz ? (uint64_t)m0 >> (32 - lz) : 0);
+    rest = rest || (uint32_t)(m0 << lz) != 0;
+    const double r = round_top64(m, rest, 32 * (top - 1) - lz - 134);  // bit 0 has the value 2^-134
     return neg ? -r : r;
   }
 };
+
+// Merge the g partials get(0) ... get(g - 1) with one block and write the
+// rounded sum (integer additions: any order gives the same digits).
+template <class Acc, class Get>
+__device__ __forceinline__ void exact_fold_partials(Get get, int g, double* out, Acc* lds) {
+  Acc s = Acc::zero();
+  for (int i = threadIdx.x; i < g; i += blockDim.x) s = Acc::merge(s, get(i));
+  s = block_reduce(s, MergeOp<Acc>{}, lds);
+  if (threadIdx.x == 0) *out = s.value();
+}
+
+// The end of pass 1: block total `s` (in every thread) to its slot, and with
+// a ticket the fold of all of them by the block that arrives last.
+template <class Acc>
+__device__ __forceinline__ void exact_fold(const Acc& s, Acc* partials, uint32_t* ticket, double* out, Acc* lds) {
+  if (gridDim.x == 1) {
+    if (threadIdx.x == 0) *out = s.value();
+    return;
+  }
+  if (!ticket) {
+    if (threadIdx.x == 0) partials[blockIdx.x] = s;
+    return;
+  }
+  __shared__ int last;
+  if (threadIdx.x == 0) {
+    publish_partial(partials, blockIdx.x, s);
+    last = arrive_last(ticket, blockIdx.x, gridDim.x);
+  }
+  __syncthreads();
+  if (last) exact_fold_partials([&](int i) { return read_partial(partials, i); }, (int)gridDim.x, out, lds);
+}
 
 // Pass 1: every block folds its grid-stride share of 16-byte vectors (8
 // values; head and tail elements by the last block) into one state.  The
@@ -124,7 +161,8 @@ constexpr int kExactMaxBlock = 512;          // 9 slots x 8 bytes x 512 threads 
 
 template <int U>
 __global__ __launch_bounds__(kExactMaxBlock) void exact_bf16_kernel(const uint16_t* __restrict__ x, Range r,
-                                                                    Bf16Exact* partials) {
+                                                                    Bf16Exact* partials, uint32_t* ticket,
+                                                                    double* out) {
   __shared__ Bf16Exact lds[kMaxWaves];
   extern __shared__ double dig[];  // (kExactFoldDigits + 1) * blockDim
   constexpr int V = 8;
@@ -201,16 +239,14 @@ __global__ __launch_bounds__(kExactMaxBlock) void exact_bf16_kernel(const uint16
   s.nf = nf;
   s.normalize();  // digits in [0, 2^32) before the cross-lane sums
   s = block_reduce(s, MergeOp<Bf16Exact>{}, lds);
-  if (tid == 0) partials[blockIdx.x] = s;
+  exact_fold(s, partials, ticket, out, lds);
 }
 
-// Pass 2 (one block): digit sums over the partials, then the rounding.
-static __global__ __launch_bounds__(256) void exact_bf16_final_kernel(const Bf16Exact* partials, int g, double* out) {
-  __shared__ Bf16Exact lds[kMaxWaves];
-  Bf16Exact s = Bf16Exact::zero();
-  for (int i = threadIdx.x; i < g; i += blockDim.x) s = Bf16Exact::merge(s, partials[i]);
-  s = block_reduce(s, MergeOp<Bf16Exact>{}, lds);
-  if (threadIdx.x == 0) *out = s.value();
+// Pass 2 (one block) of the two-launch form.
+template <class Acc>
+__global__ __launch_bounds__(256) void exact_final_kernel(const Acc* partials, int g, double* out) {
+  __shared__ Acc lds[kMaxWaves];
+  exact_fold_partials([&](int i) { return partials[i]; }, g, out, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -288,7 +324,8 @@ __device__ __forceinline__ float f16_bits_to_f32(uint32_t u) {
 template <int U, bool kVec>
 __global__ __launch_bounds__(1024) void exact_f16_dot_kernel(const uint16_t* __restrict__ x,
                                                              const uint16_t* __restrict__ z, Range r,
-                                                             F16DotExact* partials) {
+                                                             F16DotExact* partials, uint32_t* ticket,
+                                                             double* out) {
   __shared__ F16DotExact lds[kMaxWaves];
   const int64_t B = blockDim.x, tid = threadIdx.x;
   F16DotExact acc = F16DotExact::zero();
@@ -339,16 +376,7 @@ __global__ __launch_bounds__(1024) void exact_f16_dot_kernel(const uint16_t* __r
   }
   acc.flush();
   acc = block_reduce(acc, MergeOp<F16DotExact>{}, lds);
-  if (tid == 0) partials[blockIdx.x] = acc;
-}
-
-static __global__ __launch_bounds__(256) void exact_f16_dot_final_kernel(const F16DotExact* partials, int g,
-                                                                         double* out) {
-  __shared__ F16DotExact lds[kMaxWaves];
-  F16DotExact s = F16DotExact::zero();
-  for (int i = threadIdx.x; i < g; i += blockDim.x) s = F16DotExact::merge(s, partials[i]);
-  s = block_reduce(s, MergeOp<F16DotExact>{}, lds);
-  if (threadIdx.x == 0) *out = s.value();
+  exact_fold(acc, partials, ticket, out, lds);
 }
 
 }  // namespace hdc

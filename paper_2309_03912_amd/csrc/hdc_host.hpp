@@ -205,22 +205,22 @@ constexpr int64_t batch_chunk_vecs(const Tuning& t, int kvec) {
 // Per-family launchers (one translation unit each).
 hdc_status run_map(const hdc_functor& f, hdc_dtype dt, const void* x, void* y, int64_t n, const Tuning& t,
                    hipStream_t st);
-// `ticket`: NULL for the two-launch form, else a counter for the one-launch
+// `ticket`: NULL for the two-launch form, else the ticket of the one-launch
 // form (see launch_reduce).
 hdc_status run_reduce(const hdc_functor& f, hdc_dtype dt, const void* x, const void* z, int64_t n, hdc_accum acc,
-                      void* out, void* ws, uint64_t* ticket, const Tuning& t, hipStream_t st);
+                      void* out, void* ws, uint32_t* ticket, const Tuning& t, hipStream_t st);
 // Fused map + reduce, one translation unit per storage type.
 hdc_status run_map_reduce_f32(const hdc_functor& fm, const hdc_functor& f, const void* x, void* y, int64_t n,
-                              hdc_accum acc, void* out, void* ws, uint64_t* ticket, const Tuning& t,
+                              hdc_accum acc, void* out, void* ws, uint32_t* ticket, const Tuning& t,
                               hipStream_t st);
 hdc_status run_map_reduce_f16(const hdc_functor& fm, const hdc_functor& f, const void* x, void* y, int64_t n,
-                              hdc_accum acc, void* out, void* ws, uint64_t* ticket, const Tuning& t,
+                              hdc_accum acc, void* out, void* ws, uint32_t* ticket, const Tuning& t,
                               hipStream_t st);
 hdc_status run_map_reduce_bf16(const hdc_functor& fm, const hdc_functor& f, const void* x, void* y, int64_t n,
-                               hdc_accum acc, void* out, void* ws, uint64_t* ticket, const Tuning& t,
+                               hdc_accum acc, void* out, void* ws, uint32_t* ticket, const Tuning& t,
                                hipStream_t st);
 hdc_status run_map_reduce_i32(const hdc_functor& fm, const hdc_functor& f, const void* x, void* y, int64_t n,
-                              hdc_accum acc, void* out, void* ws, uint64_t* ticket, const Tuning& t,
+                              hdc_accum acc, void* out, void* ws, uint32_t* ticket, const Tuning& t,
                               hipStream_t st);
 // `ws_bytes`: the workspace's size, which sets the work-list capacity.
 hdc_status run_segmented(const hdc_functor& f, hdc_dtype dt, const void* x, const int64_t* off, int64_t nseg,

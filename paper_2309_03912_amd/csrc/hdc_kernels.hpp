@@ -294,13 +294,11 @@ template <> struct FinalFold<PlainAcc> {
   using V = float;
   using Op = AddF32;
   __device__ static V term(const PlainAcc& p) { return p.s; }
-  __device__ static V invalid() { return __builtin_nanf(""); }
   __device__ static void write(void* out, V v) { *static_cast<float*>(out) = v; }
 };
 template <> struct FinalFold<CompAcc> {
   using V = double;
   using Op = AddF64;
-  __device__ static V invalid() { return __builtin_nan(""); }
   __device__ static V term(const CompAcc& p) {
     return __builtin_isfinite(p.s) ? (double)p.s + (double)p.c : (double)p.s;
   }
@@ -310,36 +308,43 @@ template <> struct FinalFold<IntAcc> {
   using V = uint64_t;
   using Op = AddU64;
   __device__ static V term(const IntAcc& p) { return p.s; }
-  __device__ static V invalid() { return (uint64_t)INT64_MIN; }
   __device__ static void write(void* out, V v) { *static_cast<int64_t*>(out) = (int64_t)v; }
 };
 template <> struct FinalFold<ExactAcc> {
   using V = ExactAcc;
   using Op = MergeOp<ExactAcc>;
   __device__ static V term(const ExactAcc& p) { return p; }
-  __device__ static V invalid() {
-    ExactAcc a = ExactAcc::zero();
-    a.nf = __builtin_nanf("");
-    return a;
-  }
   __device__ static void write(void* out, const V& v) { *static_cast<double*>(out) = v.value(); }
 };
 
 constexpr int kFoldThreads = 256;
 
 // Every thread of the block must call this (it synchronises the block);
-// `lds` holds kFoldThreads / 64 values; get(i) returns partial i.
+// `lds` holds kFoldThreads / 64 values; get(i) returns partial i.  A virtual
+// thread loads four partials before it folds the first, all unconditionally
+// (past G it reads partial G - 1 again and does not fold it).
 template <class Acc, class Get>
 __device__ __forceinline__ void fold_partials(Get get, int G, void* out, typename FinalFold<Acc>::V* lds) {
   using FF = FinalFold<Acc>;
   using V = typename FF::V;
   const typename FF::Op op{};
   constexpr int kVW = kFoldThreads / 64;
+  constexpr int kRound = 4;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
   for (int vw = wid; vw < kVW; vw += nw) {
     V s{};
     if constexpr (std::is_same_v<Acc, ExactAcc>) s = ExactAcc::zero();
-    for (int i = vw * 64 + lane; i < G; i += kFoldThreads) s = op(s, FF::term(get(i)));
+    for (int i = vw * 64 + lane, base = vw * 64; base < G; i += kRound * kFoldThreads, base += kRound * kFoldThreads) {
+      Acc a[kRound];
+#pragma unroll
+      for (int u = 0; u < kRound; ++u) {
+        const int k = i + u * kFoldThreads;
+        a[u] = get(k < G ? k : G - 1);
+      }
+#pragma unroll
+      for (int u = 0; u < kRound; ++u)
+        if (i + u * kFoldThreads < G) s = op(s, FF::term(a[u]));
+    }
     const V w = wave_reduce(s, op);
     if (lane == 0) lds[vw] = w;
   }
@@ -353,28 +358,67 @@ __device__ __forceinline__ void fold_partials(Get get, int G, void* out, typenam
 }
 
 // ---------------------------------------------------------------------------
-// One-launch fold.  A 64-bit ticket holds (epoch << 32 | arrivals).  Every
-// block publishes its partial as sizeof(Acc) / 4 words of 64 bits, each
-// (epoch << 32 | one 32-bit word of the fold state), by single-copy-atomic
-// stores, then counts itself on the ticket.  The block that arrives last
-// reads every word until it carries the launch's epoch (so no fence orders a
-// value against a separate flag), folds the partials, and moves the ticket
-// to the next epoch with 0 arrivals.  A word keeps its tag until rewritten,
-// so a stale word could only pass for a fresh one after 2^32 launches on the
-// same workspace.
+// One-launch fold.  Every block stores its fold state with agent-scope
+// (write-through) stores, waits until they have completed, and then counts
+// itself on the ticket; the block that arrives last therefore finds every
+// partial in memory and folds them -- no tag, no flag and no wait on another
+// block.  Same-address atomics of all the chip's blocks serialize (~27 ns
+// each across the XCDs: 512 blocks cost 14 us on one counter), so arrivals
+// are counted on kTicketFan counters 256 bytes apart and the last of each
+// then on the root: 512 blocks queue 32 deep, twice.  Each counter is set
+// back to 0 by the block that completes it, so the ticket needs no
+// preparation between launches on one stream, nor inside a replayed graph.
 // ---------------------------------------------------------------------------
 
+constexpr uint32_t kTicketFan = 16;
+constexpr uint32_t kTicketStride = 64;                                 // 32-bit words between counters
+constexpr uint32_t kTicketWords = (kTicketFan + 1) * kTicketStride;    // one ticket: the root, then the fan
+
+// A fold state as machine words, and its agent-scope stores and loads.
 template <class Acc>
-constexpr int kAccWords = (int)(sizeof(Acc) / 4);
+using AccWord = std::conditional_t<sizeof(Acc) % 8 == 0, uint64_t, uint32_t>;
 
 template <class Acc>
-__device__ __forceinline__ void publish_partial(uint64_t* slots, int64_t i, const Acc& a, uint32_t epoch) {
-  uint32_t w[kAccWords<Acc>];
+__device__ __forceinline__ void publish_partial(Acc* slots, int64_t i, const Acc& a) {
+  using W = AccWord<Acc>;
+  constexpr int N = (int)(sizeof(Acc) / sizeof(W));
+  W w[N];
   __builtin_memcpy(w, &a, sizeof(Acc));
+  W* p = reinterpret_cast<W*>(slots + i);
 #pragma unroll
-  for (int k = 0; k < kAccWords<Acc>; ++k)
-    __hip_atomic_store(slots + i * kAccWords<Acc> + k, ((uint64_t)epoch << 32) | w[k], __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+  for (int k = 0; k < N; ++k) __hip_atomic_store(p + k, w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <class Acc>
+__device__ __forceinline__ Acc read_partial(const Acc* slots, int64_t i) {
+  using W = AccWord<Acc>;
+  constexpr int N = (int)(sizeof(Acc) / sizeof(W));
+  W w[N];
+  const W* p = reinterpret_cast<const W*>(slots + i);
+#pragma unroll
+  for (int k = 0; k < N; ++k) w[k] = __hip_atomic_load(p + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  Acc a;
+  __builtin_memcpy(&a, w, sizeof(Acc));
+  return a;
+}
+
+// Count block b of G on the ticket: true for the block that arrives last.
+// Called by one thread, the one that made the block's agent-scope stores:
+// the wait for them is in its own wavefront's memory counter.
+__device__ __forceinline__ bool arrive_last(uint32_t* ticket, uint32_t b, uint32_t G) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores above are complete at agent scope
+  auto count = [](uint32_t* c, uint32_t members) {
+    if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return false;
+    __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+  };
+  uint32_t groups = G;
+  if (G > 2 * kTicketFan) {
+    const uint32_t g = b % kTicketFan;
+    if (!count(ticket + (1 + g) * kTicketStride, (G - g + kTicketFan - 1) / kTicketFan)) return false;
+    groups = kTicketFan;
+  }
+  return count(ticket, groups);
 }
 
 // ---------------------------------------------------------------------------
@@ -389,7 +433,7 @@ __device__ __forceinline__ void publish_partial(uint64_t* slots, int64_t i, cons
 template <class F, class S, class Acc, int U, bool kVector, class FM = Identity, bool kMap = false>
   requires device_callable<F> && device_callable<FM>
 __global__ __launch_bounds__(1024) void reduce_kernel(F f, const elem_t<S>* x, const elem_t<S>* z, Range r,
-                                                      Acc* partials, uint64_t* ticket, void* out, FM fm = FM{},
+                                                      Acc* partials, uint32_t* ticket, void* out, FM fm = FM{},
                                                       elem_t<S>* y = nullptr) {
   __shared__ Acc lds[kMaxWaves];
   const int64_t B = blockDim.x;
@@ -531,72 +575,23 @@ __global__ __launch_bounds__(1024) void reduce_kernel(F f, const elem_t<S>* x, c
 #pragma unroll
   for (int k = 1; k < K; ++k) t = Acc::merge(t, outer[k]);
   t = block_reduce(t, MergeOp<Acc>{}, lds);
-  if (!ticket) {
+  const bool only = gridDim.x == 1;  // a single block folds its own partial: no memory, no ticket
+  if (!ticket && !only) {
     if (tid == 0) partials[blockIdx.x] = t;
-  } else {
-    // One launch: the block that arrives last folds every partial (the
-    // workspace holds the tagged words instead of plain partials).
-    __shared__ int last;
-    __shared__ uint32_t epoch_sh;
-    __shared__ typename FinalFold<Acc>::V fold_lds[kFoldThreads / 64];
-    uint64_t* slots = reinterpret_cast<uint64_t*>(partials);
+    return;
+  }
+  // One launch: the block that arrives last folds every partial.
+  __shared__ int last;
+  __shared__ typename FinalFold<Acc>::V fold_lds[kFoldThreads / 64];
+  if (!only) {
     if (tid == 0) {
-      const uint32_t epoch = (uint32_t)(__hip_atomic_load(ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32);
-      publish_partial(slots, blockIdx.x, t, epoch);
-      const uint64_t old = __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = (uint32_t)old == gridDim.x - 1;
-      epoch_sh = epoch;
+      publish_partial(partials, blockIdx.x, t);
+      last = arrive_last(ticket, blockIdx.x, gridDim.x);
     }
     __syncthreads();
-    if (last) {
-      // Stage every tagged word in LDS (dynamic, gridDim.x * kAccWords words):
-      // eight independent loads per thread per round, a word re-read only
-      // while it lacks the epoch; then fold from LDS in the fixed order.
-      extern __shared__ uint32_t stage[];
-      const uint32_t epoch = epoch_sh;
-      const int nw = (int)gridDim.x * kAccWords<Acc>;
-      bool ok = true;
-      for (int base = 0; base < nw; base += 8 * (int)B) {
-        uint64_t v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int k = base + u * (int)B + (int)tid;
-          v[u] = k < nw ? __hip_atomic_load(slots + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                        : (uint64_t)epoch << 32;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int k = base + u * (int)B + (int)tid;
-          for (int polls = 0; (uint32_t)(v[u] >> 32) != epoch; ++polls) {
-            if (polls == (1 << 20)) {
-              ok = false;
-              break;
-            }
-            __builtin_amdgcn_s_sleep(2);
-            v[u] = __hip_atomic_load(slots + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-          if (k < nw) stage[k] = (uint32_t)v[u];
-        }
-      }
-      __shared__ int all_ok;
-      if (tid == 0) all_ok = 1;
-      __syncthreads();
-      if (!ok) all_ok = 0;
-      __syncthreads();
-      fold_partials<Acc>(
-          [&](int i) {
-            Acc a;
-            __builtin_memcpy(&a, stage + (int64_t)i * kAccWords<Acc>, sizeof(Acc));
-            return a;
-          },
-          (int)gridDim.x, out, fold_lds);
-      if (tid == 0) {
-        if (!all_ok) FinalFold<Acc>::write(out, FinalFold<Acc>::invalid());
-        // arrivals back to 0, next epoch
-        __hip_atomic_fetch_add(ticket, (1ull << 32) - gridDim.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
+    if (!last) return;
   }
+  fold_partials<Acc>([&](int i) { return only ? t : read_partial(partials, i); }, (int)gridDim.x, out, fold_lds);
 }
 
 // ---------------------------------------------------------------------------

@@ -42,13 +42,13 @@ hdc_status launch_final(const Acc* partials, int64_t g, void* out, hipStream_t s
   return check_launch("final combine launch");
 }
 
-// `ticket`: a 64-bit counter (epoch, arrivals) with 0 arrivals that no other
-// work uses until this call completes; with it the reduction is one launch
-// (its last block folds the partials), without it (NULL) two launches.  Both
-// fold in the same order, so they give the same bits.
+// `ticket`: kTicketWords zero words that no other work uses until this call
+// completes; with it the reduction is one launch (its last block folds the
+// partials), without it (NULL) two launches.  Both fold in the same order, so
+// they give the same bits.
 template <class F, class S, class Acc, class FM = Identity, bool kMap = false>
 hdc_status launch_reduce(const F& f, const void* x, const void* z, int64_t n, void* out, void* ws,
-                         uint64_t* ticket, const Tuning& t, hipStream_t st, const FM& fm = FM{},
+                         uint32_t* ticket, const Tuning& t, hipStream_t st, const FM& fm = FM{},
                          void* y = nullptr) {
   using T = typename S::T;
   int cus = 0;
@@ -60,20 +60,13 @@ hdc_status launch_reduce(const F& f, const void* x, const void* z, int64_t n, vo
   const int64_t units = vec ? r.nvec : n;
   const int64_t g = grid_for(units, (int64_t)t.block * t.unroll, cus, t);
   Acc* partials = static_cast<Acc*>(ws);
-  // The one-launch form keeps 8 bytes per 32-bit word of every partial in
-  // the workspace and stages the words in LDS (at most kMaxStageBytes); a
-  // larger grid takes two launches.
-  constexpr size_t kMaxStageBytes = 32768;
-  const size_t stage = (size_t)g * kAccWords<Acc> * 4;
-  if (ticket && (2 * stage > reduce_workspace_bytes() || stage > kMaxStageBytes)) ticket = nullptr;
-  const size_t dyn = ticket ? stage : 0;
   auto go = [&](auto U) {
     constexpr int kU = decltype(U)::value;
     if (vec)
-      reduce_kernel<F, S, Acc, kU, true, FM, kMap><<<dim3((unsigned)g), dim3(t.block), dyn, st>>>(
+      reduce_kernel<F, S, Acc, kU, true, FM, kMap><<<dim3((unsigned)g), dim3(t.block), 0, st>>>(
           f, (const T*)x, (const T*)z, r, partials, ticket, out, fm, (T*)y);
     else
-      reduce_kernel<F, S, Acc, kU, false, FM, kMap><<<dim3((unsigned)g), dim3(t.block), dyn, st>>>(
+      reduce_kernel<F, S, Acc, kU, false, FM, kMap><<<dim3((unsigned)g), dim3(t.block), 0, st>>>(
           f, (const T*)x, (const T*)z, r, partials, ticket, out, fm, (T*)y);
   };
   switch (t.unroll) {
@@ -83,7 +76,7 @@ hdc_status launch_reduce(const F& f, const void* x, const void* z, int64_t n, vo
     default: go(std::integral_constant<int, 8>{}); break;
   }
   HDC_TRY(check_launch("reduce kernel launch"));
-  if (ticket) return HDC_OK;
+  if (ticket || g == 1) return HDC_OK;
   return launch_final<Acc>(partials, g, out, st);
 }
 
@@ -92,8 +85,8 @@ hdc_status launch_reduce(const F& f, const void* x, const void* z, int64_t n, vo
 // digit accumulators take 64 bytes of LDS per thread) x t.unroll vectors per
 // step (1, 2 or 4), at most 4096 blocks (their 88-byte partials fit the
 // reduce workspace), then the one-block final combine and rounding.
-inline hdc_status launch_exact_bf16(const void* x, int64_t n, void* out, void* ws, const Tuning& tuned,
-                                    hipStream_t st) {
+inline hdc_status launch_exact_bf16(const void* x, int64_t n, void* out, void* ws, uint32_t* ticket,
+                                    const Tuning& tuned, hipStream_t st) {
   int cus = 0;
   HDC_TRY(compute_units(&cus));
   Tuning t = tuned;
@@ -112,23 +105,25 @@ inline hdc_status launch_exact_bf16(const void* x, int64_t n, void* out, void* w
   if (g < g_min) g = g_min;
   Bf16Exact* partials = static_cast<Bf16Exact*>(ws);
   const uint16_t* xp = static_cast<const uint16_t*>(x);
+  double* o = static_cast<double*>(out);
   const dim3 grid((unsigned)g), block(t.block);
   const size_t lds = sizeof(double) * (kExactFoldDigits + 1) * (size_t)t.block;
   if (u == 1)
-    exact_bf16_kernel<1><<<grid, block, lds, st>>>(xp, r, partials);
+    exact_bf16_kernel<1><<<grid, block, lds, st>>>(xp, r, partials, ticket, o);
   else if (u == 2)
-    exact_bf16_kernel<2><<<grid, block, lds, st>>>(xp, r, partials);
+    exact_bf16_kernel<2><<<grid, block, lds, st>>>(xp, r, partials, ticket, o);
   else
-    exact_bf16_kernel<4><<<grid, block, lds, st>>>(xp, r, partials);
+    exact_bf16_kernel<4><<<grid, block, lds, st>>>(xp, r, partials, ticket, o);
   HDC_TRY(check_launch("exact bf16 launch"));
-  exact_bf16_final_kernel<<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, static_cast<double*>(out));
+  if (ticket || g == 1) return HDC_OK;
+  exact_final_kernel<Bf16Exact><<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, o);
   return check_launch("exact bf16 final launch");
 }
 
 // Exact fp16 dot product: vectors when x and z share their 16-byte offset,
 // else one element at a time.
 inline hdc_status launch_exact_f16_dot(const void* x, const void* z, int64_t n, void* out, void* ws,
-                                       const Tuning& t, hipStream_t st) {
+                                       uint32_t* ticket, const Tuning& t, hipStream_t st) {
   int cus = 0;
   HDC_TRY(compute_units(&cus));
   const bool vec = ((uintptr_t)x % 16) == ((uintptr_t)z % 16);
@@ -138,18 +133,20 @@ inline hdc_status launch_exact_f16_dot(const void* x, const void* z, int64_t n, 
   if (g > 4096) g = 4096;
   F16DotExact* partials = static_cast<F16DotExact*>(ws);
   const uint16_t* xp = static_cast<const uint16_t*>(x);
+  double* o = static_cast<double*>(out);
   const uint16_t* zp = static_cast<const uint16_t*>(z);
   const dim3 grid((unsigned)g), block(t.block);
   if (!vec)
-    exact_f16_dot_kernel<1, false><<<grid, block, 0, st>>>(xp, zp, r, partials);
+    exact_f16_dot_kernel<1, false><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
   else if (u == 1)
-    exact_f16_dot_kernel<1, true><<<grid, block, 0, st>>>(xp, zp, r, partials);
+    exact_f16_dot_kernel<1, true><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
   else if (u == 2)
-    exact_f16_dot_kernel<2, true><<<grid, block, 0, st>>>(xp, zp, r, partials);
+    exact_f16_dot_kernel<2, true><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
   else
-    exact_f16_dot_kernel<4, true><<<grid, block, 0, st>>>(xp, zp, r, partials);
+    exact_f16_dot_kernel<4, true><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
   HDC_TRY(check_launch("exact fp16 dot launch"));
-  exact_f16_dot_final_kernel<<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, static_cast<double*>(out));
+  if (ticket || g == 1) return HDC_OK;
+  exact_final_kernel<F16DotExact><<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, o);
   return check_launch("exact fp16 dot final launch");
 }
 

@@ -11,7 +11,7 @@
 namespace hdc {
 
 hdc_status HDC_MR_NAME(const hdc_functor& fm, const hdc_functor& f, const void* x, void* y, int64_t n,
-                       hdc_accum acc, void* out, void* ws, uint64_t* ticket, const Tuning& t, hipStream_t st) {
+                       hdc_accum acc, void* out, void* ws, uint32_t* ticket, const Tuning& t, hipStream_t st) {
   using S = HDC_MR_STORAGE;
   if constexpr (std::is_same_v<S, I32>) {
     (void)acc;

@@ -341,6 +341,7 @@ __device__ __forceinline__ void fold_partials(Get get, int G, void* out, typenam
         const int k = i + u * kFoldThreads;
         a[u] = get(k < G ? k : G - 1);
       }
+      asm volatile("" ::: "memory");  // keeps the compiler from sinking each load to its use
 #pragma unroll
       for (int u = 0; u < kRound; ++u)
         if (i + u * kFoldThreads < G) s = op(s, FF::term(a[u]));

@@ -83,7 +83,7 @@ hdc_status launch_reduce(const F& f, const void* x, const void* z, int64_t n, vo
 
 // Exact bf16 sum: pass 1 over t.block threads (at most kExactMaxBlock: the
 // digit accumulators take 64 bytes of LDS per thread) x t.unroll vectors per
-// step (1, 2 or 4), at most 4096 blocks (their 88-byte partials fit the
+// step (1, 2 or 4), at most 4096 blocks (their 48-byte partials fit the
 // reduce workspace), then the one-block final combine and rounding.
 inline hdc_status launch_exact_bf16(const void* x, int64_t n, void* out, void* ws, uint32_t* ticket,
                                     const Tuning& tuned, hipStream_t st) {
@@ -99,11 +99,11 @@ inline hdc_status launch_exact_bf16(const void* x, int64_t n, void* out, void* w
   // fp64 accumulators stay exact), within the partials the workspace holds.
   const int64_t lanes_needed = (r.nvec + kExactVecsPerLane - 1) / kExactVecsPerLane;
   const int64_t g_min = (lanes_needed + t.block - 1) / t.block;
-  constexpr int64_t kMaxExactGrid = (int64_t)(kMaxGrid * kPartialBytes / sizeof(Bf16Exact));
+  constexpr int64_t kMaxExactGrid = (int64_t)(kMaxGrid * kPartialBytes / sizeof(Bf16Partial));
   if (g_min > kMaxExactGrid)
     return fail(HDC_ERR_UNSUPPORTED, "n = %lld is too large for an exact bf16 sum at block %d", (long long)n, t.block);
   if (g < g_min) g = g_min;
-  Bf16Exact* partials = static_cast<Bf16Exact*>(ws);
+  Bf16Partial* partials = static_cast<Bf16Partial*>(ws);
   const uint16_t* xp = static_cast<const uint16_t*>(x);
   double* o = static_cast<double*>(out);
   const dim3 grid((unsigned)g), block(t.block);
@@ -116,7 +116,7 @@ inline hdc_status launch_exact_bf16(const void* x, int64_t n, void* out, void* w
     exact_bf16_kernel<4><<<grid, block, lds, st>>>(xp, r, partials, ticket, o);
   HDC_TRY(check_launch("exact bf16 launch"));
   if (ticket || g == 1) return HDC_OK;
-  exact_final_kernel<Bf16Exact><<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, o);
+  exact_bf16_final_kernel<<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, o);
   return check_launch("exact bf16 final launch");
 }
 
@@ -146,7 +146,7 @@ inline hdc_status launch_exact_f16_dot(const void* x, const void* z, int64_t n, 
     exact_f16_dot_kernel<4, true><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
   HDC_TRY(check_launch("exact fp16 dot launch"));
   if (ticket || g == 1) return HDC_OK;
-  exact_final_kernel<F16DotExact><<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, o);
+  exact_f16_dot_final_kernel<<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, o);
   return check_launch("exact fp16 dot final launch");
 }
 

@@ -315,8 +315,7 @@ typedef struct hdc_batch_call {
  * *out = the fold of g over x, each call exactly as hdc_map_reduce /
  * hdc_transform_reduce define it.  `calls` is a HOST array read during this
  * call (the table is passed to the kernels by value, so the launches can be
- * recorded into a graph).  A call whose x and y differ in 16-byte alignment
- * runs on its own.  Workspace: hdc_workspace_size(HDC_OP_BATCH, dt, acc,
+ * recorded into a graph).  Workspace: hdc_workspace_size(HDC_OP_BATCH, dt, acc,
  * sum of n, count, ...).  Reduction results depend on the tuning of
  * HDC_OP_BATCH (chunk length), not on the batch composition.
  */

@@ -436,7 +436,7 @@ hdc_status hdc_map(const hdc_functor* f, hdc_dtype dt, const void* x, void* y, i
     return fail(HDC_ERR_INVALID_ARGUMENT, "x and y overlap partially");
   const Tuning t = tuning_for(HDC_OP_MAP, dt, HDC_ACC_PLAIN, n);
   log_dispatch("map", dt, HDC_ACC_PLAIN, n, t,
-               ((uintptr_t)x % 16) == ((uintptr_t)y % 16) ? "16-byte vectors" : "scalar (x, y misaligned)", "none");
+               map_vectors(x, y, n) ? "16-byte vectors" : "scalar (x, y misaligned)", "none");
   hipStream_t st = (hipStream_t)stream;
   return run_map(*f, dt, x, y, n, t, st);
 }
@@ -595,14 +595,13 @@ hdc_status hdc_batch_map_reduce(const hdc_functor* f, const hdc_functor* g, hdc_
   const Tuning t = tuning_for(HDC_OP_BATCH, dt, acc, total / count);
   void* ws = nullptr;
   size_t need = batch_workspace_bytes(total, count);
-  if (need < reduce_workspace_bytes()) need = reduce_workspace_bytes();  // calls run one by one reuse it
+  if (need < reduce_workspace_bytes()) need = reduce_workspace_bytes();  // as hdc_workspace_size asks for
   HDC_TRY(resolve_workspace(workspace, ws_bytes, need, st, &ws));
   const size_t cap = workspace ? ws_bytes : need;  // the library's buffer holds at least `need`
   log_dispatch("batch_map_reduce", dt, acc, total / count, t, f ? "grouped map + reduce" : "grouped reduce",
                workspace ? "caller" : "library");
 
-  // Calls whose x and y disagree in 16-byte alignment run one by one; the
-  // rest go in groups of up to kBatchMax calls.
+  // Groups of up to kBatchMax calls.
   int32_t grp[kBatchMax];
   int ng = 0;
   char* wsb = static_cast<char*>(ws);  // groups run in stream order and share it
@@ -613,13 +612,6 @@ hdc_status hdc_batch_map_reduce(const hdc_functor* f, const hdc_functor* g, hdc_
     return r;
   };
   for (int32_t i = 0; i < count; ++i) {
-    const hdc_batch_call& c = calls[i];
-    const bool vec = !(f && c.y) || ((uintptr_t)c.x % 16) == ((uintptr_t)c.y % 16);
-    if (!vec) {
-      if (f && c.y)
-        HDC_TRY(hdc_map_reduce(f, g, dt, c.x, c.y, c.n, acc, c.out, ws, need, stream));
-      continue;
-    }
     grp[ng++] = i;
     if (ng == kBatchMax) HDC_TRY(flush());
   }
@@ -748,7 +740,7 @@ hdc_status hdc_workspace_size(int op, hdc_dtype dt, hdc_accum acc, int64_t n, in
       return HDC_OK;
     case HDC_OP_BATCH:
       *bytes = batch_workspace_bytes(n, num_segments);
-      if (*bytes < reduce_workspace_bytes()) *bytes = reduce_workspace_bytes();  // calls run one by one reuse it
+      if (*bytes < reduce_workspace_bytes()) *bytes = reduce_workspace_bytes();  // never less than one reduction needs
       return HDC_OK;
     case HDC_OP_SEGMENTED_REDUCE:
       if (n / kMinChunk >= INT32_MAX / 2 || num_segments >= INT32_MAX)

@@ -11,6 +11,8 @@
 namespace hdc {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));   // 16 bytes at an element of any storage type
+typedef u32x4 u32x4_word __attribute__((aligned(4)));  // 16 bytes at a 4-byte boundary
 
 // 16 bytes of storage S: 4 x fp32/int32 or 8 x fp16/bf16.
 template <class S>
@@ -18,13 +20,15 @@ struct alignas(16) Vec {
   typename S::T e[S::kVec];
 };
 
-// Streaming 16-byte load (`p` must be 16-byte aligned).  Every byte of the
-// inputs is read once, so the load is marked non-temporal: on gfx950 that
+// Streaming 16-byte load (`p` needs its element's alignment only: the same
+// global_load_dwordx4 serves every address, and a wavefront's run of 1 KiB
+// just touches one line more when it starts inside a line).  Every byte of
+// the inputs is read once, so the load is marked non-temporal: on gfx950 that
 // keeps streamed lines from displacing cache contents and measured ~7.0 TB/s
 // for a pure read against ~6.3 TB/s with the default cache policy.
 template <class S>
 __device__ __forceinline__ Vec<S> load16(const typename S::T* p) {
-  u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p));
   Vec<S> r;
   __builtin_memcpy(&r, &w, 16);
   return r;

@@ -517,10 +517,12 @@ __device__ __forceinline__ float f16_bits_to_f32(uint32_t u) {
   return (float)__builtin_bit_cast(_Float16, (uint16_t)u);
 }
 
-// Pass 1: every block folds its grid-stride share.  kVec: x and z share their
-// offset from a 16-byte boundary, so the body is 16-byte vectors of 8 values
-// (the head and the tail by the last block); otherwise every element alone.
-template <int U, bool kVec>
+// Pass 1: every block folds its grid-stride share in 16-byte vectors of 8
+// values aligned to x (the head and the tail by the last block).  kEven: z's
+// vectors start on 4-byte boundaries, as buffer loads need, and are loaded
+// through a buffer resource as x's are; otherwise they are loaded with global
+// loads, which take any address.
+template <int U, bool kEven>
 __global__ __launch_bounds__(1024) void exact_f16_dot_kernel(const uint16_t* __restrict__ x,
                                                              const uint16_t* __restrict__ z, Range r,
                                                              F16DotExact* partials, uint32_t* ticket,
@@ -528,50 +530,52 @@ __global__ __launch_bounds__(1024) void exact_f16_dot_kernel(const uint16_t* __r
   __shared__ F16DotExact lds[kMaxWaves];
   const int64_t B = blockDim.x, tid = threadIdx.x;
   F16DotExact acc = F16DotExact::zero();
-  if constexpr (kVec) {
-    constexpr int V = 8;
-    const uint16_t* xv = x + r.head;
-    const uint16_t* zv = z + r.head;
-    const int64_t cv = B * U;  // vectors per chunk
-    const int64_t nchunk = (r.nvec + cv - 1) / cv;
-    // Loads through raw buffer resources based at the chunk and ending at its
-    // last vector, as in exact_bf16_kernel: zeros past the end (a product of
-    // zeros adds nothing), fixed lane offsets.
-    uint32_t vo[U];
+  constexpr int V = 8;
+  const uint16_t* xv = x + r.head;
+  const uint16_t* zv = z + r.head;
+  const int64_t cv = B * U;  // vectors per chunk
+  const int64_t nchunk = (r.nvec + cv - 1) / cv;
+  // Loads through raw buffer resources based at the chunk and ending at its
+  // last vector, as in exact_bf16_kernel: zeros past the end (a product of
+  // zeros adds nothing), fixed lane offsets.
+  uint32_t vo[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) vo[u] = (uint32_t)(tid + u * B) * 16u;
-    for (int64_t c = blockIdx.x; c < nchunk; c += gridDim.x) {
-      const int64_t v0 = c * cv;
-      const int32_t bytes = (int32_t)((r.nvec - v0 < cv ? r.nvec - v0 : cv) * 16);
-      const __amdgpu_buffer_rsrc_t rx =
-          __builtin_amdgcn_make_buffer_rsrc((void*)(xv + v0 * V), (short)0, bytes, 0x00020000);
+  for (int u = 0; u < U; ++u) vo[u] = (uint32_t)(tid + u * B) * 16u;
+  for (int64_t c = blockIdx.x; c < nchunk; c += gridDim.x) {
+    const int64_t v0 = c * cv;
+    const int32_t bytes = (int32_t)((r.nvec - v0 < cv ? r.nvec - v0 : cv) * 16);
+    const __amdgpu_buffer_rsrc_t rx =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(xv + v0 * V), (short)0, bytes, 0x00020000);
+    u32x4 a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, vo[u], 0, 2);
+    if constexpr (kEven) {
       const __amdgpu_buffer_rsrc_t rz =
           __builtin_amdgcn_make_buffer_rsrc((void*)(zv + v0 * V), (short)0, bytes, 0x00020000);
-      u32x4 a[U], b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) b[u] = __builtin_amdgcn_raw_buffer_load_b128(rz, vo[u], 0, 2);
+    } else {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        a[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, vo[u], 0, 2);
-        b[u] = __builtin_amdgcn_raw_buffer_load_b128(rz, vo[u], 0, 2);
+        // past the end: the chunk's first vector again, replaced by zeros
+        const int64_t v = v0 + tid + u * B;
+        const Vec<F16> w = load16<F16>(reinterpret_cast<const _Float16*>(zv + (v < r.nvec ? v : v0) * V));
+        __builtin_memcpy(&b[u], &w, 16);
+        if (v >= r.nvec) b[u] = u32x4{0u, 0u, 0u, 0u};
       }
+    }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          acc.add(f16_bits_to_f32(a[u][k]) * f16_bits_to_f32(b[u][k]));          // exact in fp32
-          acc.add(f16_bits_to_f32(a[u][k] >> 16) * f16_bits_to_f32(b[u][k] >> 16));
-        }
-      acc.flush();  // chains of at most 8 U terms
-    }
-    if (blockIdx.x == gridDim.x - 1) {  // unaligned head and the tail, one element per lane
-      if (tid < r.head) acc.add(f16_bits_to_f32(x[tid]) * f16_bits_to_f32(z[tid]));
-      if (tid < r.tail) acc.add(f16_bits_to_f32(x[r.tail_start + tid]) * f16_bits_to_f32(z[r.tail_start + tid]));
-    }
-  } else {
-    for (int64_t c = blockIdx.x; c * B < r.n; c += gridDim.x) {
-      const int64_t i = c * B + tid;
-      if (i < r.n) acc.add(f16_bits_to_f32(x[i]) * f16_bits_to_f32(z[i]));
-      acc.flush();
-    }
+      for (int k = 0; k < 4; ++k) {
+        acc.add(f16_bits_to_f32(a[u][k]) * f16_bits_to_f32(b[u][k]));          // exact in fp32
+        acc.add(f16_bits_to_f32(a[u][k] >> 16) * f16_bits_to_f32(b[u][k] >> 16));
+      }
+    acc.flush();  // chains of at most 8 U terms
+  }
+  if (blockIdx.x == gridDim.x - 1) {  // unaligned head and the tail, one element per lane
+    if (tid < r.head) acc.add(f16_bits_to_f32(x[tid]) * f16_bits_to_f32(z[tid]));
+    if (tid < r.tail) acc.add(f16_bits_to_f32(x[r.tail_start + tid]) * f16_bits_to_f32(z[r.tail_start + tid]));
   }
   acc.flush();
   acc = block_reduce(acc, MergeOp<F16DotExact>{}, lds);

@@ -15,10 +15,12 @@
 
 namespace hdc {
 
-// How an array of n elements is walked.  Vector mode: `head` leading
-// elements up to the first 16-byte boundary, `nvec` aligned 16-byte vectors,
-// then `tail` trailing elements starting at `tail_start`.  Scalar mode (used
-// when two operands disagree in alignment): all n elements one by one.
+// How an array of n elements is walked: `head` leading elements up to the
+// first 16-byte boundary, `nvec` aligned 16-byte vectors, then `tail` trailing
+// elements starting at `tail_start`.  With several operands the boundaries are
+// those of the one that is stored (else of x); the others are loaded 16 bytes
+// at a time from wherever they start.  (The map's scalar walk takes all n
+// elements one by one.)
 struct Range {
   int64_t n;
   int64_t head;
@@ -431,7 +433,7 @@ __device__ __forceinline__ bool arrive_last(uint32_t* ticket, uint32_t b, uint32
 // With kMap, the same pass also writes y[i] = fm(x[i]) (fused map + reduce).
 // ---------------------------------------------------------------------------
 
-template <class F, class S, class Acc, int U, bool kVector, class FM = Identity, bool kMap = false>
+template <class F, class S, class Acc, int U, class FM = Identity, bool kMap = false>
   requires device_callable<F> && device_callable<FM>
 __global__ __launch_bounds__(1024) void reduce_kernel(F f, const elem_t<S>* x, const elem_t<S>* z, Range r,
                                                       Acc* partials, uint32_t* ticket, void* out, FM fm = FM{},
@@ -445,8 +447,8 @@ __global__ __launch_bounds__(1024) void reduce_kernel(F f, const elem_t<S>* x, c
   // eight of them (one per fp16 of a vector) overflow the register file, so
   // it keeps two; each fp64 chain then takes at most kFlush * N / 2 <= 256
   // terms between flushes, far inside the exact state's 2^13.
-  constexpr int K = std::is_same_v<Acc, ExactAcc> ? 2 : (kVector ? S::kVec : U);
-  constexpr int N = kVector ? U * S::kVec : U;  // elements per lane per step
+  constexpr int K = std::is_same_v<Acc, ExactAcc> ? 2 : S::kVec;
+  constexpr int N = U * S::kVec;  // elements per lane per step
   // Two-level fold: `acc` takes the terms of at most kFlush steps, then is
   // merged into `outer`.  A plain fp32 chain then never grows longer than
   // kFlush * U terms plus one term per kFlush steps, whatever the grid size,
@@ -487,86 +489,63 @@ __global__ __launch_bounds__(1024) void reduce_kernel(F f, const elem_t<S>* x, c
     }
   };
 
-  if constexpr (kVector) {
-    const elem_t<S>* xv = x + r.head;
-    const elem_t<S>* zv = F::binary ? z + r.head : nullptr;
-    const int64_t nchunk = (r.nvec + B * U - 1) / (B * U);
-    auto step = [&](int64_t base, auto full_c) {
-      constexpr bool kFull = decltype(full_c)::value;
-      Vec<S> a[U], b[U];
+  const elem_t<S>* xv = x + r.head;
+  const elem_t<S>* zv = F::binary ? z + r.head : nullptr;
+  const int64_t nchunk = (r.nvec + B * U - 1) / (B * U);
+  auto step = [&](int64_t base, auto full_c) {
+    constexpr bool kFull = decltype(full_c)::value;
+    Vec<S> a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (kFull || base + u * B < r.nvec) {
+        a[u] = load16<S>(xv + (base + u * B) * S::kVec);
+        if constexpr (F::binary) b[u] = load16<S>(zv + (base + u * B) * S::kVec);
+      } else {
+        a[u] = Vec<S>{};
+        b[u] = Vec<S>{};
+      }
+    }
+    elem_t<S> v[N], w[N];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int k = 0; k < S::kVec; ++k) {
+        v[u * S::kVec + k] = a[u].e[k];
+        w[u * S::kVec + k] = F::binary ? b[u].e[k] : a[u].e[k];
+      }
+    }
+    fold_step(v, w, [&](int i) { return kFull || base + (i / S::kVec) * B < r.nvec; });
+    if constexpr (kMap) {
+      elem_t<S> o[N];
+      map_batch<FM, S>(fm, v, o);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (kFull || base + u * B < r.nvec) {
-          a[u] = load16<S>(xv + (base + u * B) * S::kVec);
-          if constexpr (F::binary) b[u] = load16<S>(zv + (base + u * B) * S::kVec);
-        } else {
-          a[u] = Vec<S>{};
-          b[u] = Vec<S>{};
+          Vec<S> ov;
+#pragma unroll
+          for (int k = 0; k < S::kVec; ++k) ov.e[k] = o[u * S::kVec + k];
+          store16_nt<S>(y + r.head + (base + u * B) * S::kVec, ov);
         }
-      }
-      elem_t<S> v[N], w[N];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int k = 0; k < S::kVec; ++k) {
-          v[u * S::kVec + k] = a[u].e[k];
-          w[u * S::kVec + k] = F::binary ? b[u].e[k] : a[u].e[k];
-        }
-      }
-      fold_step(v, w, [&](int i) { return kFull || base + (i / S::kVec) * B < r.nvec; });
-      if constexpr (kMap) {
-        elem_t<S> o[N];
-        map_batch<FM, S>(fm, v, o);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if (kFull || base + u * B < r.nvec) {
-            Vec<S> ov;
-#pragma unroll
-            for (int k = 0; k < S::kVec; ++k) ov.e[k] = o[u * S::kVec + k];
-            store16_nt<S>(y + r.head + (base + u * B) * S::kVec, ov);
-          }
-        }
-      }
-    };
-    for (int64_t c = blockIdx.x; c < nchunk; c += gridDim.x) {
-      const int64_t base = c * B * U + tid;
-      if (c * B * U + B * U <= r.nvec)
-        step(base, std::true_type{});
-      else
-        step(base, std::false_type{});
-      if constexpr (std::is_same_v<Acc, PlainAcc> || std::is_same_v<Acc, ExactAcc>) maybe_flush();
-    }
-    if (blockIdx.x == gridDim.x - 1) {
-      if (tid < r.head) {
-        fold_elem<F, S>(acc[0], f, x[tid], F::binary ? z[tid] : x[tid]);
-        if constexpr (kMap) y[tid] = map_elem<FM, S>(fm, x[tid]);
-      }
-      if (tid < r.tail) {
-        const int64_t i = r.tail_start + tid;
-        fold_elem<F, S>(acc[1 % K], f, x[i], F::binary ? z[i] : x[i]);
-        if constexpr (kMap) y[i] = map_elem<FM, S>(fm, x[i]);
       }
     }
-  } else {
-    const int64_t stride = (int64_t)gridDim.x * B;
-    for (int64_t i = blockIdx.x * B + tid; i < r.n; i += stride * U) {
-      elem_t<S> v[N], w[N];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool ok = i + u * stride < r.n;
-        v[u] = ok ? x[i + u * stride] : elem_t<S>{};
-        if constexpr (F::binary) w[u] = ok ? z[i + u * stride] : elem_t<S>{};
-        else w[u] = v[u];
-      }
-      fold_step(v, w, [&](int u) { return i + u * stride < r.n; });
-      if constexpr (std::is_same_v<Acc, PlainAcc> || std::is_same_v<Acc, ExactAcc>) maybe_flush();
-      if constexpr (kMap) {
-        elem_t<S> o[N];
-        map_batch<FM, S>(fm, v, o);
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (i + u * stride < r.n) y[i + u * stride] = o[u];
-      }
+  };
+  for (int64_t c = blockIdx.x; c < nchunk; c += gridDim.x) {
+    const int64_t base = c * B * U + tid;
+    if (c * B * U + B * U <= r.nvec)
+      step(base, std::true_type{});
+    else
+      step(base, std::false_type{});
+    if constexpr (std::is_same_v<Acc, PlainAcc> || std::is_same_v<Acc, ExactAcc>) maybe_flush();
+  }
+  if (blockIdx.x == gridDim.x - 1) {
+    if (tid < r.head) {
+      fold_elem<F, S>(acc[0], f, x[tid], F::binary ? z[tid] : x[tid]);
+      if constexpr (kMap) y[tid] = map_elem<FM, S>(fm, x[tid]);
+    }
+    if (tid < r.tail) {
+      const int64_t i = r.tail_start + tid;
+      fold_elem<F, S>(acc[1 % K], f, x[i], F::binary ? z[i] : x[i]);
+      if constexpr (kMap) y[i] = map_elem<FM, S>(fm, x[i]);
     }
   }
 

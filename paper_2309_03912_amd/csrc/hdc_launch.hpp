@@ -16,8 +16,8 @@ hdc_status launch_map(const F& f, const void* x, void* y, int64_t n, const Tunin
   using T = typename S::T;
   int cus = 0;
   HDC_TRY(compute_units(&cus));
-  const bool vec = ((uintptr_t)x % 16) == ((uintptr_t)y % 16);
-  Range r = make_range<S>(x, n, vec);
+  const bool vec = map_vectors(x, y, n);
+  const Range r = vec ? make_range<S>(y, n) : Range{n, 0, 0, 0, 0};
   const int64_t units = vec ? r.nvec : n;
   const int64_t g = grid_for(units, (int64_t)t.block * t.unroll, cus, t);
   auto go = [&](auto U) {
@@ -53,21 +53,13 @@ hdc_status launch_reduce(const F& f, const void* x, const void* z, int64_t n, vo
   using T = typename S::T;
   int cus = 0;
   HDC_TRY(compute_units(&cus));
-  bool vec = true;
-  if (F::binary && ((uintptr_t)x % 16) != ((uintptr_t)z % 16)) vec = false;
-  if (kMap && ((uintptr_t)x % 16) != ((uintptr_t)y % 16)) vec = false;
-  Range r = make_range<S>(x, n, vec);
-  const int64_t units = vec ? r.nvec : n;
-  const int64_t g = grid_for(units, (int64_t)t.block * t.unroll, cus, t);
+  const Range r = make_range<S>(kMap ? y : x, n);
+  const int64_t g = grid_for(r.nvec, (int64_t)t.block * t.unroll, cus, t);
   Acc* partials = static_cast<Acc*>(ws);
   auto go = [&](auto U) {
     constexpr int kU = decltype(U)::value;
-    if (vec)
-      reduce_kernel<F, S, Acc, kU, true, FM, kMap><<<dim3((unsigned)g), dim3(t.block), 0, st>>>(
-          f, (const T*)x, (const T*)z, r, partials, ticket, out, fm, (T*)y);
-    else
-      reduce_kernel<F, S, Acc, kU, false, FM, kMap><<<dim3((unsigned)g), dim3(t.block), 0, st>>>(
-          f, (const T*)x, (const T*)z, r, partials, ticket, out, fm, (T*)y);
+    reduce_kernel<F, S, Acc, kU, FM, kMap><<<dim3((unsigned)g), dim3(t.block), 0, st>>>(
+        f, (const T*)x, (const T*)z, r, partials, ticket, out, fm, (T*)y);
   };
   switch (t.unroll) {
     case 1: go(std::integral_constant<int, 1>{}); break;
@@ -91,7 +83,7 @@ inline hdc_status launch_exact_bf16(const void* x, int64_t n, void* out, void* w
   HDC_TRY(compute_units(&cus));
   Tuning t = tuned;
   if (t.block > kExactMaxBlock) t.block = kExactMaxBlock;
-  const Range r = make_range<BF16>(x, n, true);
+  const Range r = make_range<BF16>(x, n);
   const int u = t.unroll >= 4 ? 4 : t.unroll;
   int64_t g = grid_for(r.nvec, (int64_t)t.block * u, cus, t);
   if (g > 4096) g = 4096;
@@ -120,30 +112,33 @@ inline hdc_status launch_exact_bf16(const void* x, int64_t n, void* out, void* w
   return check_launch("exact bf16 final launch");
 }
 
-// Exact fp16 dot product: vectors when x and z share their 16-byte offset,
-// else one element at a time.
+// Exact fp16 dot product, in vectors aligned to x.
 inline hdc_status launch_exact_f16_dot(const void* x, const void* z, int64_t n, void* out, void* ws,
                                        uint32_t* ticket, const Tuning& t, hipStream_t st) {
   int cus = 0;
   HDC_TRY(compute_units(&cus));
-  const bool vec = ((uintptr_t)x % 16) == ((uintptr_t)z % 16);
-  const Range r = make_range<F16>(x, n, vec);
-  const int u = !vec ? 1 : t.unroll >= 4 ? 4 : t.unroll;
-  int64_t g = grid_for(vec ? r.nvec : n, (int64_t)t.block * u, cus, t);
+  const Range r = make_range<F16>(x, n);
+  const bool even = ((uintptr_t)z - (uintptr_t)x) % 4 == 0;
+  const int u = t.unroll >= 4 ? 4 : t.unroll;
+  int64_t g = grid_for(r.nvec, (int64_t)t.block * u, cus, t);
   if (g > 4096) g = 4096;
   F16DotExact* partials = static_cast<F16DotExact*>(ws);
   const uint16_t* xp = static_cast<const uint16_t*>(x);
   double* o = static_cast<double*>(out);
   const uint16_t* zp = static_cast<const uint16_t*>(z);
   const dim3 grid((unsigned)g), block(t.block);
-  if (!vec)
-    exact_f16_dot_kernel<1, false><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
-  else if (u == 1)
-    exact_f16_dot_kernel<1, true><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
-  else if (u == 2)
-    exact_f16_dot_kernel<2, true><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
-  else
-    exact_f16_dot_kernel<4, true><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
+  auto go = [&](auto U) {
+    constexpr int kU = decltype(U)::value;
+    if (even)
+      exact_f16_dot_kernel<kU, true><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
+    else
+      exact_f16_dot_kernel<kU, false><<<grid, block, 0, st>>>(xp, zp, r, partials, ticket, o);
+  };
+  switch (u) {
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    default: go(std::integral_constant<int, 4>{}); break;
+  }
   HDC_TRY(check_launch("exact fp16 dot launch"));
   if (ticket || g == 1) return HDC_OK;
   exact_f16_dot_final_kernel<<<dim3(1), dim3(256), 0, st>>>(partials, (int)g, o);
@@ -250,8 +245,8 @@ hdc_status launch_segmented(const F& f, const void* x, const int64_t* off, int64
 }
 
 template <class FM, class F, class S, class Acc>
-hdc_status launch_batch(const FM& fm, const F& f, const hdc_batch_call* calls, const int32_t* idx, int cnt,
-                        void* ws, size_t ws_bytes, const Tuning& t, hipStream_t st) {
+hdc_status launch_batch(const FM& fm, bool maps, const F& f, const hdc_batch_call* calls, const int32_t* idx,
+                        int cnt, void* ws, size_t ws_bytes, const Tuning& t, hipStream_t st) {
   int cus = 0;
   HDC_TRY(compute_units(&cus));
   BatchTable tab{};
@@ -262,9 +257,9 @@ hdc_status launch_batch(const FM& fm, const F& f, const hdc_batch_call* calls, c
     const hdc_batch_call& c = calls[idx[q]];
     BatchCall& b = tab.call[q];
     b.x = c.x;
-    b.y = c.y;
+    b.y = maps ? c.y : nullptr;
     b.out = c.out;
-    b.r = make_range<S>(c.x, c.n, true);
+    b.r = make_range<S>(b.y ? b.y : c.x, c.n);
     tab.prefix[q] = acc_chunks;
     if (c.n > 0) {
       int64_t nc = (b.r.nvec + tab.chunk_vecs - 1) / tab.chunk_vecs;
@@ -311,7 +306,8 @@ hdc_status launch_scan(const F& f, const void* x, void* y, int64_t n, int exclus
   const int64_t tile = (int64_t)t.block * kScanE;
   const int64_t G = (n + tile - 1) / tile;
   if (G * t.block > (int64_t)UINT32_MAX) return fail(HDC_ERR_UNSUPPORTED, "n = %lld is too large for one scan", (long long)n);
-  const bool xa = (uintptr_t)x % 16 == 0, ya = (uintptr_t)y % 16 == 0;
+  // 2-byte storage that does not start on 4-byte boundaries takes global loads
+  const bool even = (uintptr_t)x % 4 == 0;
   const T* xp = static_cast<const T*>(x);
   OutT* yp = static_cast<OutT*>(y);
   const dim3 grid((unsigned)G), block(t.block);
@@ -322,35 +318,27 @@ hdc_status launch_scan(const F& f, const void* x, void* y, int64_t n, int exclus
     const int64_t cb = (nwords + 255) / 256;
     scan_lb_clear_kernel<<<dim3((unsigned)(cb < 1024 ? cb : 1024)), dim3(256), 0, st>>>(w, nwords);
     HDC_TRY(check_launch("scan look-back clear launch"));
-    if (xa && ya)
-      scan_onepass_kernel<F, S, Acc, true, true><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
-    else if (xa)
-      scan_onepass_kernel<F, S, Acc, true, false><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
-    else if (ya)
-      scan_onepass_kernel<F, S, Acc, false, true><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
-    else
-      scan_onepass_kernel<F, S, Acc, false, false><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
+    if (sizeof(T) == 4 || even)
+      scan_onepass_kernel<F, S, Acc, true><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
+    else if constexpr (sizeof(T) < 4)
+      scan_onepass_kernel<F, S, Acc, false><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
     return check_launch("scan single-pass launch");
   }
   // three passes: the same 256-byte header (its status word cleared by the
   // offsets pass), then the tile sums and the tile offsets
   Acc* sums = reinterpret_cast<Acc*>(static_cast<char*>(ws) + 256);
   Acc* offsets = reinterpret_cast<Acc*>(static_cast<char*>(ws) + 256 + round_up((size_t)G * sizeof(Acc), 256));
-  if (xa)
+  if (sizeof(T) == 4 || even)
     scan_tile_sums_kernel<F, S, Acc, true><<<grid, block, 0, st>>>(f, xp, n, seg, sums);
-  else
+  else if constexpr (sizeof(T) < 4)
     scan_tile_sums_kernel<F, S, Acc, false><<<grid, block, 0, st>>>(f, xp, n, seg, sums);
   HDC_TRY(check_launch("scan tile-sum launch"));
   scan_offsets_kernel<Acc><<<dim3(1), dim3(1024), 0, st>>>(sums, G, offsets, static_cast<uint32_t*>(ws) + 1);
   HDC_TRY(check_launch("scan offset launch"));
-  if (xa && ya)
-    scan_tiles_kernel<F, S, Acc, true, true><<<grid, block, 0, st>>>(f, xp, n, seg, offsets, yp, exclusive);
-  else if (xa)
-    scan_tiles_kernel<F, S, Acc, true, false><<<grid, block, 0, st>>>(f, xp, n, seg, offsets, yp, exclusive);
-  else if (ya)
-    scan_tiles_kernel<F, S, Acc, false, true><<<grid, block, 0, st>>>(f, xp, n, seg, offsets, yp, exclusive);
-  else
-    scan_tiles_kernel<F, S, Acc, false, false><<<grid, block, 0, st>>>(f, xp, n, seg, offsets, yp, exclusive);
+  if (sizeof(T) == 4 || even)
+    scan_tiles_kernel<F, S, Acc, true><<<grid, block, 0, st>>>(f, xp, n, seg, offsets, yp, exclusive);
+  else if constexpr (sizeof(T) < 4)
+    scan_tiles_kernel<F, S, Acc, false><<<grid, block, 0, st>>>(f, xp, n, seg, offsets, yp, exclusive);
   return check_launch("scan tile launch");
 }
 

@@ -209,19 +209,25 @@ struct ScanWave {
 
   __device__ int64_t index(int q, int e) const { return wbase + (int64_t)q * 64 * V + (int64_t)lane * V + e; }
 
-  template <bool kAligned>
+  // kEven: x starts on a 4-byte boundary, as buffer loads need.
+  template <bool kEven>
   __device__ void load(const elem_t<S>* x, const SegSpec& seg) {
-    if (kAligned && wbase + 64 * kScanE <= n) {
-      // a raw buffer resource over this wavefront's part (word 3 0x00020000:
-      // 32-bit data format, no swizzle; cache policy 2: non-temporal), so the
-      // lane offsets stay fixed instead of 64-bit address arithmetic per load
-      const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-          (void*)(x + wbase), (short)0, (int)(64 * kScanE * sizeof(elem_t<S>)), 0x00020000);
+    if (wbase + 64 * kScanE <= n) {
       Vec<S> a[Q];
+      if constexpr (kEven) {
+        // a raw buffer resource over this wavefront's part (word 3 0x00020000:
+        // 32-bit data format, no swizzle; cache policy 2: non-temporal), so the
+        // lane offsets stay fixed instead of 64-bit address arithmetic per load
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)(x + wbase), (short)0, (int)(64 * kScanE * sizeof(elem_t<S>)), 0x00020000);
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rx, (uint32_t)(q * 64 + lane) * 16u, 0, 2);
-        __builtin_memcpy(&a[q], &w, 16);
+        for (int q = 0; q < Q; ++q) {
+          const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rx, (uint32_t)(q * 64 + lane) * 16u, 0, 2);
+          __builtin_memcpy(&a[q], &w, 16);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) a[q] = load16<S>(x + index(q, 0));
       }
 #pragma unroll
       for (int q = 0; q < Q; ++q)
@@ -357,10 +363,10 @@ struct ScanWave {
   // bytes, then takes the 16-byte pieces at lanes l and 64 + l of the
   // chunk's output, so that each non-temporal store instruction of the
   // wavefront covers one contiguous KiB.
-  template <bool kOutAligned>
   __device__ void emit(const F& f, const Acc& before, int exclusive, OutT* y, u32x4* stage) const {
     constexpr int PER = 16 / sizeof(OutT);
-    bool full = kOutAligned && wbase + 64 * kScanE <= n;
+    // y needs its element's alignment only: the same 16-byte stores serve every address
+    bool full = wbase + 64 * kScanE <= n;
     if constexpr (kSeg) full = full && wbase >= out_lo && wbase + 64 * kScanE <= out_hi;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -382,7 +388,7 @@ struct ScanWave {
           __builtin_amdgcn_wave_barrier();
           const u32x4 r0 = stage[lane], r1 = stage[64 + lane];
           __builtin_amdgcn_wave_barrier();  // the next chunk's writes come after these reads
-          u32x4* p = reinterpret_cast<u32x4*>(y + index(q, 0) - (int64_t)lane * V);  // the chunk's start
+          u32x4_word* p = reinterpret_cast<u32x4_word*>(y + index(q, 0) - (int64_t)lane * V);  // the chunk's start
           __builtin_nontemporal_store(r0, p + lane);
           __builtin_nontemporal_store(r1, p + 64 + lane);
         } else {
@@ -390,7 +396,7 @@ struct ScanWave {
           for (int h = 0; h < V / PER; ++h) {
             u32x4 w;
             __builtin_memcpy(&w, &o[h * PER], 16);
-            u32x4* p = reinterpret_cast<u32x4*>(y + index(q, h * PER));
+            u32x4_word* p = reinterpret_cast<u32x4_word*>(y + index(q, h * PER));
             if constexpr (V == PER)
               __builtin_nontemporal_store(w, p);
             else
@@ -507,7 +513,7 @@ __device__ void tile_heads(W& w, const SegSpec& seg, const HeadProbe& pr, int64_
 }
 
 // Pass A: the sum of every tile.
-template <class F, class S, class Acc, bool kAligned>
+template <class F, class S, class Acc, bool kEven>
   requires device_callable<F>
 __global__ __launch_bounds__(1024) void scan_tile_sums_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
                                                               Acc* sums) {
@@ -517,7 +523,7 @@ __global__ __launch_bounds__(1024) void scan_tile_sums_kernel(F f, const elem_t<
   auto w = scan_wave_at<F, S, Acc>(blockIdx.x, n);
   HeadProbe pr{0, 0};
   if constexpr (IsSeg<Acc>::value) pr = heads_probe(seg);
-  w.template load<kAligned>(x, seg);
+  w.template load<kEven>(x, seg);
   if constexpr (IsSeg<Acc>::value)
     tile_heads(w, seg, pr, (int64_t)blockIdx.x * blockDim.x * kScanE, (int64_t)blockDim.x * kScanE, heads_sh,
                wfirst_sh);
@@ -569,7 +575,7 @@ __global__ __launch_bounds__(1024) void scan_offsets_kernel(const Acc* sums, int
 }
 
 // Pass C: scan every tile again and add its offset.
-template <class F, class S, class Acc, bool kAligned, bool kOutAligned>
+template <class F, class S, class Acc, bool kEven>
   requires device_callable<F>
 __global__ __launch_bounds__(1024) void scan_tiles_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
                                                           const Acc* offsets, typename ScanOut<Acc>::T* y,
@@ -581,14 +587,14 @@ __global__ __launch_bounds__(1024) void scan_tiles_kernel(F f, const elem_t<S>* 
   auto w = scan_wave_at<F, S, Acc>(blockIdx.x, n);
   HeadProbe pr{0, 0};
   if constexpr (IsSeg<Acc>::value) pr = heads_probe(seg);
-  w.template load<kAligned>(x, seg);
+  w.template load<kEven>(x, seg);
   if constexpr (IsSeg<Acc>::value)
     tile_heads(w, seg, pr, (int64_t)blockIdx.x * blockDim.x * kScanE, (int64_t)blockDim.x * kScanE, heads_sh,
                wfirst_sh);
   w.fold(f);
   Acc total;
   const Acc before = block_wave_prefix(w.wave_total, lds, &total);
-  w.template emit<kOutAligned>(f, Acc::merge(offsets[blockIdx.x], before), exclusive, y,
+  w.emit(f, Acc::merge(offsets[blockIdx.x], before), exclusive, y,
                                stage_sh + (threadIdx.x >> 6) * 128);
 }
 
@@ -865,7 +871,7 @@ struct OnepassWaves : std::integral_constant<int, 1> {};
 template <>
 struct OnepassWaves<SegAcc<PlainAcc>> : std::integral_constant<int, 8> {};
 
-template <class F, class S, class Acc, bool kAligned, bool kOutAligned>
+template <class F, class S, class Acc, bool kEven>
   requires device_callable<F>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(OnepassWaves<Acc>::value))) void
 scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
@@ -887,7 +893,7 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   __syncthreads();
   const int64_t tile = tile_sh;
   auto w = scan_wave_at<F, S, Acc>(tile, n);
-  w.template load<kAligned>(x, seg);
+  w.template load<kEven>(x, seg);
   if constexpr (IsSeg<Acc>::value)
     tile_heads(w, seg, pr, tile * blockDim.x * kScanE, (int64_t)blockDim.x * kScanE, heads_sh, wfirst_sh);
   w.fold(f);
@@ -903,7 +909,7 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
     if constexpr (IsSeg<Acc>::value) w.unstash(park_sh);
   }
   __syncthreads();
-  w.template emit<kOutAligned>(f, Acc::merge(C::to(carry_sh), before), exclusive, y,
+  w.emit(f, Acc::merge(C::to(carry_sh), before), exclusive, y,
                                stage_sh + (threadIdx.x >> 6) * 128);
 }
 

@@ -203,11 +203,13 @@ hdc_status hdc_transform_reduce_noalloc(const hdc_functor* f, hdc_dtype dt,
  *   round trip; hdc_validate_offsets checks it synchronously).
  *   out: S floats (PLAIN), doubles (COMPENSATED) or int64 (EXACT_INT).
  *   Empty segments give 0.  No host synchronisation (with a workspace).
- *   Two schedules, chosen by the tuning's `passes`: tiled (1) streams fixed
- *   tiles of the element range and folds the segments that span tiles in a
- *   second launch; planned (2) builds work lists in three small launches,
- *   runs one persistent pass over them and a combine launch.  Both give
- *   reproducible bits for a fixed tuning.
+ *   Two schedules, chosen by the tuning's `passes`: tiled (1, the default)
+ *   streams fixed tiles of the element range and folds the segments that span
+ *   tiles, in the same launch when the workspace is sized for few elements
+ *   (up to ~1000 tiles) and in a second one otherwise; planned (2) builds work
+ *   lists in three small launches, runs one persistent pass over them and a
+ *   combine launch.  Both give reproducible bits for a fixed tuning and
+ *   workspace size.
  *   IDENTITY, AFFINE, HORNER as for transform_reduce (no PRODUCT).
  *   workspace: at least hdc_workspace_size(HDC_OP_SEGMENTED_REDUCE, dt, acc,
  *   total, S) bytes for a total >= offsets[S]; its size sets the capacity
@@ -364,15 +366,16 @@ hdc_status hdc_validate_offsets(const int64_t* offsets, int64_t num_segments,
  * how many small segments share one wavefront (power of two, 1..64, each
  * served by 64/seg_per_wave lanes).  For HDC_OP_SCAN, block sets the tile
  * (block * 16 elements) and unroll 1 selects the three-pass schedule.
- * passes, 1 or 2 (default 2; 1 for the reductions of buckets 0..2).
+ * passes, 1 or 2 (default 2; 1 for the reductions of buckets 0..2 and for the
+ * segmented reduce).
  * HDC_OP_TRANSFORM_REDUCE, HDC_OP_DOT, HDC_OP_MAP_REDUCE: 1 folds the
  * per-block partials in the same launch, in the block that arrives last on a
  * ticket (library-owned device memory, one per workspace buffer and stream; a
  * call that finds none left takes two launches); 2 folds them in a second
  * launch (none when the grid is one block).  Both fold in the same order, so
  * `passes` does not change any result bit.  HDC_OP_SEGMENTED_REDUCE: 1
- * selects the tiled schedule (fixed tiles of `chunk` elements, no plan), 2
- * the planned one (pieces of `chunk`, packed small segments).  Tuning changes
+ * selects the tiled schedule (fixed tiles of `chunk` elements, fewer where
+ * that would leave fewer than 512 tiles; no plan), 2 the planned one (pieces of `chunk`, packed small segments).  Tuning changes
  * the summation order, so the last bits of a floating-point sum may change;
  * results stay within the stated tolerance. */
 typedef struct hdc_tuning {

@@ -146,29 +146,53 @@ inline hdc_status launch_exact_f16_dot(const void* x, const void* z, int64_t n, 
 }
 
 // Tiled schedule of the segmented reduce (t.passes == 1): the tile pass and
-// the combine of segments that span tiles.  The workspace holds two slot
-// arrays (`first`, `last`) of one 32-byte fold state per tile.
+// the fold of segments that span tiles, in the same launch when the block
+// that arrives last can hold all tiles, else in a second one.  The workspace
+// is counted in two halves of 32 bytes per tile.
+//
+// `total` bounds the elements (it comes with the workspace).  Few elements are
+// cut into smaller tiles than the tuning's, down to kMinChunk elements, while
+// there are fewer tiles than kMinTiles: with 4096 elements a tile, 300,000
+// would occupy 73 of the chip's 1024 SIMDs.
+constexpr int64_t kMinTiles = 512;
+
 template <class F, class S, class Acc>
-hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64_t nseg, void* out, void* ws,
-                            size_t ws_bytes, const Tuning& t, hipStream_t st) {
+hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64_t nseg, int64_t total, void* out,
+                            void* ws, size_t ws_bytes, uint32_t* ticket, const Tuning& t, hipStream_t st) {
   using T = typename S::T;
-  static_assert(sizeof(Acc) <= kPartialBytes, "a tile slot holds 32 bytes");
   int cus = 0;
   HDC_TRY(compute_units(&cus));
   const size_t half = ws_bytes / 2 / 256 * 256;
+  const int block = t.block < kTilesMaxBlock ? t.block : kTilesMaxBlock;
+  int64_t tile = t.chunk;
+  while (tile > kMinChunk && total / tile < kMinTiles) tile /= 2;
   SegTiles tl;
-  tl.first = ws;
-  tl.last = static_cast<char*>(ws) + half;
   tl.cap = (int64_t)(half / kPartialBytes);
-  tl.tile_vecs = t.chunk / S::kVec;
-  const int64_t wpb = t.block / 64;
+  tl.first = static_cast<uint64_t*>(ws);
+  tl.last = reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + half);
+  tl.meta = tl.first + tl.cap;  // 8 of a slot's 32 bytes are its fold state
+  tl.tile_vecs = tile / S::kVec;
+  int64_t tiles = total / tile + 2;  // at most: the head joins the first tile, the tail the last
+  if (tiles > tl.cap) tiles = tl.cap;
+  if (tiles > seg_last_tiles(block)) ticket = nullptr;
+  // one launch: a range of more elements than the workspace is sized for must not exceed the block's tiles
+  if (ticket && tl.cap > seg_last_tiles(block)) tl.cap = seg_last_tiles(block);
+  tl.one = ticket != nullptr;
+  const int64_t wpb = block / 64;
   int64_t g = (int64_t)cus * t.grid_mult;
-  const int64_t need = (tl.cap + wpb - 1) / wpb;  // never more wavefronts than tiles fit the workspace
+  const int64_t need = (tiles + wpb - 1) / wpb;  // never more wavefronts than tiles
   if (g > need) g = need;
   if (g < 1) g = 1;
+  const bool dense = ticket || nseg * kDenseVecs * S::kVec > total;
   auto go = [&](auto U) {
     constexpr int kU = decltype(U)::value;
-    seg_tiles_kernel<F, S, Acc, kU><<<dim3((unsigned)g), dim3(t.block), 0, st>>>(f, (const T*)x, off, nseg, tl, out);
+    if (dense)
+      seg_tiles_kernel<F, S, Acc, kU, true>
+          <<<dim3((unsigned)g), dim3(block), sizeof(DenseLds<S, Acc>) * (size_t)wpb, st>>>(f, (const T*)x, off, nseg,
+                                                                                         tl, ticket, out);
+    else
+      seg_tiles_kernel<F, S, Acc, kU, false><<<dim3((unsigned)g), dim3(block), 0, st>>>(f, (const T*)x, off, nseg, tl,
+                                                                                       ticket, out);
   };
   switch (t.unroll) {
     case 1: go(std::integral_constant<int, 1>{}); break;
@@ -177,6 +201,7 @@ hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64
     default: go(std::integral_constant<int, 8>{}); break;
   }
   HDC_TRY(check_launch("segmented tile launch"));
+  if (ticket) return HDC_OK;
   int64_t gc = (nseg + 255) / 256;  // one wavefront per 64 segments
   if (gc > (int64_t)cus * 8) gc = (int64_t)cus * 8;
   seg_tiles_combine_kernel<S, Acc><<<dim3((unsigned)gc), dim3(256), 0, st>>>((const T*)x, off, nseg, tl, out);
@@ -184,10 +209,11 @@ hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64
 }
 
 template <class F, class S, class Acc>
-hdc_status launch_segmented(const F& f, const void* x, const int64_t* off, int64_t nseg, void* out, void* ws,
-                            size_t ws_bytes, const Tuning& t, hipStream_t st) {
+hdc_status launch_segmented(const F& f, const void* x, const int64_t* off, int64_t nseg, int64_t total, void* out,
+                            void* ws, size_t ws_bytes, uint32_t* ticket, const Tuning& t, hipStream_t st) {
   using T = typename S::T;
-  if (t.passes == 1) return launch_seg_tiles<F, S, Acc>(f, x, off, nseg, out, ws, ws_bytes, t, st);
+  if (t.passes == 1)
+    return launch_seg_tiles<F, S, Acc>(f, x, off, nseg, total, out, ws, ws_bytes, ticket, t, st);
   int cus = 0;
   HDC_TRY(compute_units(&cus));
   const int64_t cap = seg_capacity(ws_bytes, nseg);

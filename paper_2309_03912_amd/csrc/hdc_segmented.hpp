@@ -420,27 +420,62 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int64_t* __restr
 // every wavefront streams whole tiles (w, w + W, ...) exactly as the plain
 // reduction streams its share: U vectors per lane per step, all loads of a
 // step in flight together.  The segment boundaries inside a tile come from
-// the offsets, 64 at a time in one vector register; each step first adds its
-// terms to the lanes' fold states, and only when a boundary falls inside the
-// step does the wavefront split the step's terms at it, reduce the part that
-// ends there (wave_reduce) and store it.  A segment that starts and ends
+// the offsets, 64 at a time in one vector register.  A step's chunks (one
+// vector per lane) take one of three ways by the number of segment ends
+// inside: none -- the terms are added to the lanes' fold states; a few -- the
+// wavefront splits the terms at each end, reduces the part before it
+// (wave_reduce) and stores it; more (kDenseEnds) -- one segmented scan of the
+// chunk across the wavefront, after which every lane stores the result of one
+// segment (TileWave::dense).  A segment that starts and ends
 // inside one tile is written to `out` directly.  Otherwise each tile writes
 // its part of that segment to one of two slots (`first`: the segment was open
 // when the tile started; `last`: it started in the tile and runs past its
-// end), and a second small launch folds, in tile order, the parts of every
-// segment that spans tiles (and writes 0 for empty segments).  No plan is
-// built, and the work of every wavefront is the same number of vectors.
+// end), and the parts of a segment that spans tiles are folded in tile order:
+// for few tiles by the block that arrives last in the same launch, else by a
+// second small launch (which also writes 0 for empty segments; in one launch
+// the tile that reaches their position does).  No plan is built, and the work of every wavefront is the same number of vectors.
 // The unaligned head of the range belongs to the first tile, its tail to the
 // last one.  Everything is a fold of fixed values in a fixed order, so the
 // results are reproducible bit for bit.
 // ===========================================================================
 
+// What a tile did (one launch only): the segment open at the tile's start
+// (started earlier) ended in it -- its index + 1 in the low half, else 0 -- or
+// ran through it (kTileThrough); and whether the tile wrote `last`.
+constexpr uint64_t kTileThrough = uint64_t(1) << 32;
+constexpr uint64_t kTileLast = uint64_t(1) << 33;
+
 struct SegTiles {
-  void* first;        // per tile: its part of the segment open at its start
-  void* last;         // per tile: its part of a segment starting in it and running past its end
+  uint64_t* first;    // per tile: its part of the segment open at its start (a fold state's words)
+  uint64_t* last;     // per tile: its part of a segment starting in it and running past its end
+  uint64_t* meta;     // per tile, in one launch: what it did
   int64_t cap;        // tiles the workspace holds
   int64_t tile_vecs;  // 16-byte vectors per tile
+  int32_t one;        // one launch: the block that arrives last folds the slots
 };
+
+// In one launch the slots are stored write-through at agent scope: the block
+// that folds them may run on another XCD.  (For a second launch ordinary
+// stores do, and 16,000 tiles' write-through ones took 2.6 us of 106.)
+__device__ __forceinline__ void put_word(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t get_word(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class Acc>
+__device__ __forceinline__ uint64_t acc_word(const Acc& a) {
+  static_assert(sizeof(Acc) <= 8);
+  uint64_t w = 0;
+  __builtin_memcpy(&w, &a, sizeof(Acc));
+  return w;
+}
+template <class Acc>
+__device__ __forceinline__ Acc word_acc(uint64_t w) {
+  Acc a;
+  __builtin_memcpy(&a, &w, sizeof(Acc));
+  return a;
+}
 
 // Geometry of the streamed range, from off[0] and off[S] (read on the device).
 struct TileGeom {
@@ -548,7 +583,29 @@ struct SegFinder {
   }
 };
 
-template <class F, class S, class Acc, int U>
+// Segment ends inside a chunk from which the scan is cheaper than splitting
+// the chunk at each.  A split costs ~45 instructions (plain f32; ~150
+// compensated), the scan ~100 (~250) whatever the number of ends.
+constexpr int kDenseEnds = 3;
+// Segments of fewer than this many 16-byte vectors on average (1.5 chunks) go
+// to the pass that has the scan (kDense), and so do calls that take one
+// launch; its 20-40 registers more cost longer segments 5-20%.  1.34e8 elements in lognormal segments, without ->
+// with the scan, us: f32 plain, mean 100: 258.6 -> 188.9, 200: 170.6 -> 162.3,
+// 400: 128.9 -> 137.0; bf16 compensated, mean 100: 390 -> 143, 400: 141 ->
+// 111, 800: 96.1 -> 97.4.
+constexpr int64_t kDenseVecs = 96;
+
+// LDS of the scan, per wavefront: a bit per position of the chunk, the lanes'
+// prefixes, and the running fold at every position.
+template <class S, class Acc>
+struct DenseLds {
+  alignas(16) Acc vals[64 * S::kVec];
+  Acc pre[64];
+  uint32_t bits[2 * S::kVec];
+};
+constexpr int kTilesMaxBlock = 512;  // at most 8 wavefronts' DenseLds: 37 KiB
+
+template <class F, class S, class Acc, int U, bool kDense>
 struct TileWave {
   static constexpr int KV = S::kVec;
   static constexpr int K = U * KV;  // elements per lane per step
@@ -562,6 +619,7 @@ struct TileWave {
   int32_t S_;
   SegTiles st;
   void* out;
+  DenseLds<S, Acc>* lds;
   int lane;
   int32_t tile;
   int64_t base;     // position (relative to off[0]) of the tile's first element
@@ -570,14 +628,25 @@ struct TileWave {
   int32_t j;        // the segment holding the next position
   int32_t nb;       // its end (off[j + 1] - off[0] - base), clamped to len + 1
   bool started;     // it starts inside this tile
-  int32_t bbase;    // offsets[bbase + l] are in lane l of `bnd`
+  bool lane0;       // every lane's fold state but lane 0's is zero
+  uint32_t ended;   // index + 1 of the segment open at the tile's start, once it has ended; else 0
+  int32_t bbase;    // offsets[bbase + l] are in lane l of `bnd`; bbase <= j
   int64_t bnd;      // a batch of 64 offsets (relative to off[0]); past off[S]: INT64_MAX
   Acc acc;
 
+  // A batch's offset in this lane.  The empty asm hides where it came from:
+  // knowing that lanes past off[S] hold a constant, the compiler moved the
+  // read_lane of a batch into the path of the other lanes alone, where it
+  // read a lane that was not running.
+  __device__ void set_batch(int64_t v) {
+    asm volatile("" : "+v"(v));
+    bnd = v;
+  }
   __device__ void load_batch(int32_t b) {
     bbase = b;
     const int64_t i = (int64_t)b + lane;
-    bnd = i <= S_ ? off[i] - lo : INT64_MAX;
+    const int64_t o = off[i <= S_ ? i : S_];
+    set_batch(i <= S_ ? o - lo : INT64_MAX);
   }
   // off[i] - off[0] - base, clamped to len + 1: from the batch when it
   // holds offset i, else read on its own (a uniform load)
@@ -590,10 +659,10 @@ struct TileWave {
     v -= base;
     return v <= len ? (int32_t)v : len + 1;
   }
-  // Before a step: a batch more than half used is reloaded from the next
-  // segment end on, so the boundaries of a step read their offsets from it.
+  // Before a step: a batch more than half used is reloaded from the current
+  // segment on, so the boundaries of a step read their offsets from it.
   __device__ void refill() {
-    if (j + 1 - bbase >= 32) load_batch(j + 1);
+    if (j - bbase >= 32) load_batch(j);
   }
 
   // The segment holding tile position 0 (the last j with off[j] - off[0] <=
@@ -601,83 +670,219 @@ struct TileWave {
   __device__ void locate(SegFinder& fd) {
     while (!fd.final_round()) fd.next(off, S_, lane);
     bbase = fd.a;
-    bnd = fd.probe == INT64_MAX ? INT64_MAX : fd.probe - lo;
+    set_batch(fd.probe == INT64_MAX ? INT64_MAX : fd.probe - lo);
     const int cnt = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < fd.n && bnd <= base));
     j = fd.a + cnt - 1;
     started = read_lane(bnd, j - bbase) >= base;
     nb = bound(j + 1);
   }
 
+  __device__ void put(uint64_t* p, uint64_t v) const {
+    if (kDense && st.one)
+      put_word(p, v);
+    else
+      *p = v;
+  }
   // Store the fold of a segment part that ends inside this tile.
   __device__ void finish(const Acc& total) {
     if (lane == 0 && j < S_) {
       if (started)
         store_result<Acc>(out, j, total);
       else
-        static_cast<Acc*>(st.first)[tile] = total;
+        put(&st.first[tile], acc_word(total));
     }
+    if (kDense && !started) ended = (uint32_t)j + 1;
   }
-  // Leave segment j at its end nb: the next non-empty segment starts there.
+  // Leave segment j at its end nb: the next non-empty segment starts there
+  // (the empty ones before it get 0).
   __device__ void advance() {
     const int32_t b = nb;
-    do {
+    for (;;) {
       ++j;
       nb = bound(j + 1);
-    } while (nb == b);
+      if (nb != b) break;
+      if (kDense && lane == 0) store_result<Acc>(out, j, Acc::zero());
+    }
     started = true;
   }
-
-  // Add a step's terms.  Term k sits at tile position ps + lp + dk(k), with
-  // lp this lane's offset and dk(k) a constant, and exists iff kFull or
-  // ok(k); every position of the step lies in [ps, pe).  A bound on the
-  // position is a uniform bound on lp, so the step keeps one per-lane value
-  // instead of K.
-  template <bool kFull, class Dk, class Ok>
-  __device__ void step(const Term (&t)[K], int32_t lp, Dk dk, Ok ok, int32_t ps, int32_t pe) {
-    if (nb >= pe) {  // no boundary inside the step (uniform)
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (kFull || ok(k)) acc.add(t[k]);
-      return;
+  // 0 to the empty segments from index i on that end at position `pos` (relative to off[0]).
+  __device__ void zero_empty(int32_t i, int64_t pos) {
+    for (;; i += 64) {
+      const int32_t k = i + lane;
+      const bool empty = k < S_ && off[(int64_t)k + 1] - lo == pos;
+      if (empty) store_result<Acc>(out, k, Acc::zero());
+      if (~__builtin_amdgcn_ballot_w64(empty) != 0) break;
     }
+  }
+
+  // Split N terms at the segment ends below pe: term k sits at tile position
+  // ps + lp + dk(k), with lp this lane's offset and dk(k) a constant; the
+  // positions lie in [ps, pe), and the terms past pe are 0.  A bound on the
+  // position is a uniform bound on lp, so the split keeps one per-lane value
+  // instead of N.
+  template <int N, class Dk>
+  __device__ void split(const Term (&t)[N], int32_t lp, Dk dk, int32_t ps, int32_t pe) {
     int32_t prev = 0;  // terms before ps + prev are already folded
     while (nb < pe) {
       const int32_t end = nb - ps;
 #pragma unroll
-      for (int k = 0; k < K; ++k)
-        acc.add((kFull || ok(k)) && lp >= prev - dk(k) && lp < end - dk(k) ? t[k] : Term{});
+      for (int k = 0; k < N; ++k)
+        acc.add(lp >= prev - dk(k) && lp < end - dk(k) ? t[k] : Term{});
       finish(wave_reduce(acc, MergeOp<Acc>{}));
       acc = Acc::zero();
       prev = end;
       advance();
     }
 #pragma unroll
-    for (int k = 0; k < K; ++k) acc.add((kFull || ok(k)) && lp >= prev - dk(k) ? t[k] : Term{});
+    for (int k = 0; k < N; ++k) acc.add(lp >= prev - dk(k) ? t[k] : Term{});
   }
 
-  __device__ void terms(const elem_t<S> (&v)[K], Term (&t)[K]) {
+  // Add a chunk's terms: this lane's KV terms sit at tile positions cs + lane
+  // KV + e; those from ce on are 0.
+  __device__ void chunk(const Term (&t)[KV], int32_t cs, int32_t ce) {
+    if (nb >= ce) {  // no segment end inside (uniform)
+#pragma unroll
+      for (int e = 0; e < KV; ++e) acc.add(t[e]);
+      lane0 = false;
+      return;
+    }
+    if (j - bbase >= 48) load_batch(j);
+    const int ends = __builtin_popcountll(__builtin_amdgcn_ballot_w64(bbase + lane > j && bnd - base < ce));
+    if (ends < kDenseEnds) {
+      split<KV>(t, lane * KV, [](int k) { return k; }, cs, ce);
+      lane0 = false;
+    } else {
+      dense(t, cs, ce);
+    }
+  }
+
+  // A chunk with many segment ends, by one segmented scan.  The batch's lanes
+  // mark the segment starts of the chunk in a bitmap; every lane folds its KV
+  // terms, starting over at each mark, and leaves the running fold of every
+  // position in LDS; the lanes' last folds are scanned across the wavefront
+  // (DPP moves, a lane takes part until its last mark); then lane l takes the
+  // segment whose start it holds in the batch: the running fold at its last
+  // position, joined with the prefix of that position's lane if the segment
+  // started before it, is its result.  What is left of the last segment stays
+  // in lane 0's fold state.
+  __device__ void dense(const Term (&t)[KV], int32_t cs, int32_t ce) {
+    const Acc open = lane0 ? read_lane(acc, 0) : wave_reduce(acc, MergeOp<Acc>{});
+    if (lane < 2 * KV) lds->bits[lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    const int32_t b0 = bbase;
+    auto more = [&]() { return read_lane(bnd, 63) - base < ce; };  // the batch ends inside the chunk
+    for (;;) {
+      const int64_t o = bnd - base - cs;
+      if (bbase + lane > j && o < ce - cs) atomicOr(&lds->bits[(uint32_t)o >> 5], 1u << ((uint32_t)o & 31));
+      __builtin_amdgcn_wave_barrier();
+      if (!more()) break;
+      load_batch(bbase + 63);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t at = (uint32_t)lane * KV;
+    const uint32_t marks = (lds->bits[at >> 5] >> (at & 31)) & ((1u << KV) - 1u);
+    Acc a = Acc::zero();
+#pragma unroll
+    for (int e = 0; e < KV; ++e) {
+      if (e > 0 && ((marks >> e) & 1u)) a = Acc::zero();
+      a.add(t[e]);
+      lds->vals[at + e] = a;
+    }
+    const uint64_t M = __builtin_amdgcn_ballot_w64(marks != 0);
+    const uint64_t upto = M & ((uint64_t(2) << lane) - 1);               // marked lanes up to this one
+    const int dist = upto ? lane - (63 - __builtin_clzll(upto)) : 64;    // lanes since the last of them
+    const int r = lane & 15, rd = r < dist ? r : dist;
+    {
+      const Acc u = dpp_words<0x111, 0xF>(a);
+      if (rd >= 1) a = Acc::merge(u, a);
+    }
+    {
+      const Acc u = dpp_words<0x112, 0xF>(a);
+      if (rd >= 2) a = Acc::merge(u, a);
+    }
+    {
+      const Acc u = dpp_words<0x114, 0xF>(a);
+      if (rd >= 4) a = Acc::merge(u, a);
+    }
+    {
+      const Acc u = dpp_words<0x118, 0xF>(a);
+      if (rd >= 8) a = Acc::merge(u, a);
+    }
+    {
+      const Acc u = dpp_words<0x142, 0xA>(a);  // row_bcast:15
+      if ((lane & 16) && dist > r) a = Acc::merge(u, a);
+    }
+    {
+      const Acc u = dpp_words<0x143, 0xC>(a);  // row_bcast:31
+      if (lane >= 32 && dist >= lane - 31) a = Acc::merge(u, a);
+    }
+    Acc before = dpp_words<0x138, 0xF>(a);  // wave_shr:1
+    if (lane == 0) before = Acc::zero();
+    if ((M & ((uint64_t(1) << lane) - 1)) == 0) before = Acc::merge(open, before);
+    lds->pre[lane] = before;
+    const Acc end = read_lane(a, 63);
+    const Acc rest = M ? end : Acc::merge(open, end);
+    __builtin_amdgcn_wave_barrier();
+    if (bbase != b0) load_batch(b0);
+    for (;;) {
+      const int64_t s = bnd - base - cs;
+      int64_t e = dpp_words<0x130, 0xF>(bnd) - base - cs;
+      e = lane == 63 ? INT64_MAX : e;  // wave_shl:1 gives the next offset; lane 63 has none
+      const int32_t i = bbase + lane;
+      if (i >= j && e < ce - cs) {  // segment i ends inside the chunk
+        Acc v = Acc::zero();
+        if (e > s) {
+          const int32_t p = (int32_t)e - 1;
+          if (p < 0) {
+            v = open;
+          } else {
+            v = lds->vals[p];
+            if (s < (p & ~(KV - 1))) v = Acc::merge(lds->pre[p / KV], v);
+          }
+        }
+        if (i == j && !started)
+          put(&st.first[tile], acc_word(v));
+        else
+          store_result<Acc>(out, i, v);
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (!more()) break;
+      load_batch(bbase + 63);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (!started) ended = (uint32_t)j + 1;
+    j = bbase + __builtin_popcountll(__builtin_amdgcn_ballot_w64(bnd - base < ce)) - 1;
+    nb = bound(j + 1);
+    started = true;
+    acc = lane == 0 ? rest : Acc::zero();
+    lane0 = true;
+  }
+
+  template <int N>
+  __device__ void terms(const elem_t<S> (&v)[N], Term (&t)[N]) {
     if constexpr (kInt) {
 #pragma unroll
-      for (int k = 0; k < K; ++k) t[k] = f.term(v[k]);
+      for (int k = 0; k < N; ++k) t[k] = f.term(v[k]);
     } else {
-      float w[K];
+      float w[N];
 #pragma unroll
-      for (int k = 0; k < K; ++k) w[k] = S::widen(v[k]);
-      step_terms<F, K>(f, w);
+      for (int k = 0; k < N; ++k) w[k] = S::widen(v[k]);
+      step_terms<F, N>(f, w);
 #pragma unroll
-      for (int k = 0; k < K; ++k) t[k] = w[k];
+      for (int k = 0; k < N; ++k) t[k] = w[k];
     }
   }
 
   // A step of single elements: lane l takes tile position p0 + l if below p1.
   __device__ void scalar_step(int32_t p0, int32_t p1) {
     const bool mine = p0 + lane < p1;
-    elem_t<S> v[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = k == 0 && mine ? x[base + p0 + lane] : elem_t<S>{};
-    Term t[K];
-    terms(v, t);
-    step<false>(t, lane, [](int) { return 0; }, [&](int k) { return k == 0 && mine; }, p0, p1);
+    elem_t<S> v[1];
+    v[0] = mine ? x[base + p0 + lane] : elem_t<S>{};
+    Term t[1];
+    terms<1>(v, t);
+    if (!mine) t[0] = Term{};
+    split<1>(t, lane, [](int) { return 0; }, p0, p1);
+    lane0 = false;
   }
 
   // Tile position 0 of tile t, relative to off[0].
@@ -698,6 +903,7 @@ struct TileWave {
     const int32_t vpos = (int32_t)(g.head + vb * KV - base);  // tile position of vector vb
     const elem_t<S>* xv = x + g.head + vb * KV;             // vector vb
     const int32_t nvt = (int32_t)(ve - vb);                 // vectors of the tile
+    constexpr int32_t kStep = 64 * U;
     // Two steps of loads in flight: step s + 1's loads go out before step s
     // is folded.
     Vec<S> a[U], nx[U];
@@ -730,6 +936,10 @@ struct TileWave {
     if (next >= 0) fd.start(off, S_, lo + tile_base(g, st.tile_vecs, next), lane);
     bool searching = next >= 0;
     acc = Acc::zero();
+    lane0 = true;
+    ended = 0;
+    if (kDense && first_tile)  // the segments before the first non-empty one
+      for (int32_t i = lane; i < j; i += 64) store_result<Acc>(out, i, Acc::zero());
 
     if (first_tile && g.head > 0) scalar_step(0, (int32_t)g.head);
     // Fold the step at vector v0 from buffer d.
@@ -741,16 +951,39 @@ struct TileWave {
 #pragma unroll
         for (int e = 0; e < KV; ++e) v[u * KV + e] = d[u].e[e];
       Term t[K];
-      terms(v, t);
+      terms<K>(v, t);
+      const int32_t ps = vpos + v0 * KV;
+      const int32_t nv = nvt - v0;  // vectors of the step, if below 64 U
+      if (nv < 64 * U) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+          if (lane + (k / KV) * 64 >= nv) t[k] = Term{};
+      }
       // term (u, e) is element e of vector v0 + 64 u + lane: step position
       // lane * KV + (64 u KV + e)
-      auto dk = [](int k) { return (k / KV) * 64 * KV + k % KV; };
-      const int32_t ps = vpos + v0 * KV;
-      if (v0 + 64 * U <= nvt) {
-        step<true>(t, lane * KV, dk, [](int) { return true; }, ps, ps + 64 * U * KV);
+      if (nb >= ps + kStep * KV) {  // no segment end inside (uniform)
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc.add(t[k]);
+        if constexpr (kDense) lane0 = false;
+      } else if constexpr (!kDense) {
+        split<K>(t, lane * KV, [](int k) { return (k / KV) * 64 * KV + k % KV; }, ps,
+                 ps + (nv < 64 * U ? nv : 64 * U) * KV);
       } else {
-        const int32_t nv = nvt - v0;
-        step<false>(t, lane * KV, dk, [&](int k) { return lane < nv - (k / KV) * 64; }, ps, ps + nv * KV);
+        // The chunks run in a loop (the terms picked by selects, uniform in
+        // u): the code of the three ways once per fold, not U times --
+        // unrolled, the pass with U = 2 ran four times slower than with U = 1.
+#pragma unroll 1
+        for (int u = 0; u < U && 64 * u < nv; ++u) {
+          Term tc[KV];
+#pragma unroll
+          for (int e = 0; e < KV; ++e) {
+            tc[e] = t[e];
+#pragma unroll
+            for (int q = 1; q < U; ++q) tc[e] = u == q ? t[q * KV + e] : tc[e];
+          }
+          const int32_t cs = ps + 64 * u * KV, left = nv - 64 * u;
+          chunk(tc, cs, cs + (left < 64 ? left : 64) * KV);
+        }
       }
       if (searching) {  // one round of the next tile's search per step
         if (fd.final_round())
@@ -760,43 +993,128 @@ struct TileWave {
       }
     };
     // Steps in pairs, the two buffers taking turns, so that no buffer is
-    // copied (a copy would wait for the loads in flight).
-    // Every pair the loop starts has both steps (an odd last step follows
-    // it), so the loads of each buffer are always folded before the buffer
-    // is loaded again.  The loads for the step after the pair go out
-    // unconditionally (past the tile's end they return zeros and are never
-    // folded): a load issued on one path only makes the compiler's wait for
-    // the other buffer count it as absent, so the next fold would wait for
-    // every load in flight.
-    constexpr int32_t kStep = 64 * U;
+    // copied (a copy would wait for the loads in flight).  The loads of both
+    // buffers go out unconditionally (past the tile's end they return zeros
+    // and are never folded): a load issued on one path only makes the
+    // compiler's wait for the other buffer count it as absent, so the next
+    // fold would wait for every load in flight.
     int32_t v0 = 0;
-    for (; v0 + kStep < nvt; v0 += 2 * kStep) {
+    for (; kDense ? v0 < nvt : v0 + kStep < nvt; v0 += 2 * kStep) {
       issue(nx, v0 + kStep);
       fold(a, v0);
       issue(a, v0 + 2 * kStep);
-      fold(nx, v0 + kStep);
+      if (!kDense || v0 + kStep < nvt) fold(nx, v0 + kStep);
     }
-    if (v0 < nvt) fold(a, v0);
+    if (!kDense && v0 < nvt) fold(a, v0);  // (a third copy of the fold, which the scan's code is too large for)
     if (last_tile && g.tail_start < g.n) scalar_step((int32_t)(g.tail_start - base), len);
 
     // The segment open at the tile's end: it ends exactly there, or runs on.
     const Acc total = wave_reduce(acc, MergeOp<Acc>{});
+    uint64_t meta = 0;
     if (nb == len) {
       finish(total);
-    } else if (lane == 0) {
-      if (started)
-        static_cast<Acc*>(st.last)[tile] = total;
-      else
-        static_cast<Acc*>(st.first)[tile] = total;
+      if constexpr (kDense) zero_empty(j + 1, base + len);
+    } else if (started) {
+      if (lane == 0) put(&st.last[tile], acc_word(total));
+      meta = kTileLast;
+    } else {
+      if (lane == 0) put(&st.first[tile], acc_word(total));
+      meta = kTileThrough;
     }
+    if (kDense && st.one && lane == 0) put(&st.meta[tile], meta | ended);
   }
 };
 
-template <class F, class S, class Acc, int U>
+// The fold of segments that span tiles, by one block: every lane takes a
+// tile, in tile order, and a segmented scan over what each tile passes on to
+// the next (its part of a segment that runs through it, or the start of a new
+// one) gives every tile the sum of the open segment before it.  A wavefront
+// keeps up to kLastRounds tiles per lane in registers, all loaded at once.
+constexpr int kLastRounds = 4;
+// Tiles one block of `block` threads folds.
+constexpr int64_t seg_last_tiles(int block) { return (int64_t)block * kLastRounds; }
+
+template <class V>
+struct OpenSum {
+  V v;
+  uint32_t start;  // a segment starts inside the span
+  uint32_t pad;
+  __device__ static OpenSum zero() { return {V{}, 0u, 0u}; }
+  __device__ static OpenSum merge(const OpenSum& a, const OpenSum& b) {
+    return b.start ? b : OpenSum{a.v + b.v, a.start, 0u};
+  }
+};
+
+// What a part of a segment counts as in the fold over its tiles.
+__device__ __forceinline__ float part_value(const PlainAcc& a) { return a.s; }
+__device__ __forceinline__ double part_value(const CompAcc& a) { return comp_value(a); }
+__device__ __forceinline__ uint64_t part_value(const IntAcc& a) { return a.s; }
+__device__ __forceinline__ void store_value(void* out, int64_t j, float v) { static_cast<float*>(out)[j] = v; }
+__device__ __forceinline__ void store_value(void* out, int64_t j, double v) { static_cast<double*>(out)[j] = v; }
+__device__ __forceinline__ void store_value(void* out, int64_t j, uint64_t v) {
+  static_cast<int64_t*>(out)[j] = (int64_t)v;
+}
+
+template <class Acc>
+__device__ __forceinline__ void seg_fold_last(const SegTiles& st, int32_t ntiles, void* out) {
+  using V = decltype(part_value(Acc::zero()));
+  using P = OpenSum<V>;
+  __shared__ P totals[kMaxWaves];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int32_t rounds = (ntiles + nw * 64 - 1) / (nw * 64);  // <= kLastRounds
+  uint64_t fw[kLastRounds], lw[kLastRounds], mw[kLastRounds];
+#pragma unroll
+  for (int r = 0; r < kLastRounds; ++r) {
+    const int32_t t = (wid * rounds + r) * 64 + lane;
+    const int32_t k = t < ntiles ? t : ntiles - 1;
+    if (r < rounds) {
+      fw[r] = get_word(&st.first[k]);
+      lw[r] = get_word(&st.last[k]);
+      mw[r] = get_word(&st.meta[k]);
+    }
+  }
+  P incl[kLastRounds], run = P::zero();
+#pragma unroll
+  for (int r = 0; r < kLastRounds; ++r) {
+    if (r < rounds) {
+      const bool in = (wid * rounds + r) * 64 + lane < ntiles;
+      if (!in) mw[r] = 0;
+      P x = P::zero();
+      if (mw[r] & kTileThrough) {
+        x.v = part_value(word_acc<Acc>(fw[r]));
+      } else if (in) {
+        if (mw[r] & kTileLast) x.v = part_value(word_acc<Acc>(lw[r]));
+        x.start = 1;
+      }
+      incl[r] = wave_incl_scan(x);
+      run = P::merge(run, read_lane(incl[r], 63));
+    }
+  }
+  if (lane == 0) totals[wid] = run;
+  __syncthreads();
+  P open = P::zero();
+  for (int w = 0; w < wid; ++w) open = P::merge(open, totals[w]);
+#pragma unroll
+  for (int r = 0; r < kLastRounds; ++r) {
+    if (r < rounds) {
+      const P before = P::merge(open, wave_shift_up1(incl[r], P::zero()));
+      const uint32_t ended = (uint32_t)mw[r];  // segment index + 1
+      if (ended) store_value(out, (int64_t)ended - 1, before.v + part_value(word_acc<Acc>(fw[r])));
+      open = P::merge(open, read_lane(incl[r], 63));
+    }
+  }
+}
+
+// What bounds it: HBM where segment ends are rare, the vector ALU where there
+// are many (kDenseEnds).  `ticket`: the one-launch form (at most
+// seg_last_tiles(blockDim.x) tiles, which the launcher knows from the
+// workspace): the block that arrives last folds the segments that span tiles.
+template <class F, class S, class Acc, int U, bool kDense>
   requires device_callable<F>
-__global__ __launch_bounds__(1024) void seg_tiles_kernel(F f, const elem_t<S>* __restrict__ x,
-                                                         const int64_t* __restrict__ off, int64_t S_, SegTiles st,
-                                                         void* out) {
+__global__ __launch_bounds__(kTilesMaxBlock) void seg_tiles_kernel(F f, const elem_t<S>* __restrict__ x,
+                                                                   const int64_t* __restrict__ off, int64_t S_,
+                                                                   SegTiles st, uint32_t* ticket, void* out) {
+  extern __shared__ char dense_lds[];
   const int lane = threadIdx.x & 63;
   const int64_t wpb = blockDim.x >> 6;
   const int64_t w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * wpb + (threadIdx.x >> 6)));
@@ -806,26 +1124,35 @@ __global__ __launch_bounds__(1024) void seg_tiles_kernel(F f, const elem_t<S>* _
   SegFinder fd{};
   fd.begin(off, (int32_t)S_, lane);
   const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
-  if (g.ntiles > st.cap) {
-    // More tiles than the workspace holds: every segment is folded whole by one wavefront.
+  // More tiles than the workspace holds: every segment is folded whole by
+  // one wavefront.  (No element at all: every segment is empty.)
+  if (g.ntiles > st.cap || g.ntiles == 0) {
     for (int64_t j = w; j < S_; j += W) {
       const Acc r = wave_fold_range<F, S, Acc, U>(f, x, off[j], off[j + 1], lane);
       if (lane == 0) store_result<Acc>(out, j, r);
     }
-    return;
+    return;  // (so does every other block: none arrives at the ticket)
   }
+  DenseLds<S, Acc>* lds = kDense ? reinterpret_cast<DenseLds<S, Acc>*>(dense_lds) + (threadIdx.x >> 6) : nullptr;
   bool have = true;
   for (int64_t t = w; t < g.ntiles; t += W) {
-    TileWave<F, S, Acc, U> tw{f, x + g.lo, off, g.lo, (int32_t)S_, st, out, lane, (int32_t)t};
+    TileWave<F, S, Acc, U, kDense> tw{f, x + g.lo, off, g.lo, (int32_t)S_, st, out, lds, lane, (int32_t)t};
     const int64_t next = t + W < g.ntiles ? t + W : -1;
     tw.run(g, fd, have, next);
     have = next >= 0;
   }
+  if (!kDense || !ticket) return;
+  __shared__ int last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's slots are complete at agent scope
+  __syncthreads();
+  if (threadIdx.x == 0) last = arrive_last(ticket, blockIdx.x, gridDim.x);
+  __syncthreads();
+  if (last) seg_fold_last<Acc>(st, (int32_t)g.ntiles, out);
 }
 
-// Segments that span tiles: their parts folded in tile order (the part of
-// the tile where the segment starts, then every later tile's `first` part);
-// empty segments: 0.  Each lane takes one segment; a segment spanning more
+// Segments that span tiles (the two-launch form): their parts folded in tile
+// order (the part of the tile where the segment starts, then every later
+// tile's `first` part).  Each lane takes one segment; a segment spanning more
 // than kLaneTiles tiles is folded by the whole wavefront (wave_fold_items).
 constexpr int64_t kLaneTiles = 16;
 
@@ -834,12 +1161,12 @@ __global__ __launch_bounds__(256) void seg_tiles_combine_kernel(const elem_t<S>*
                                                                 const int64_t* __restrict__ off, int64_t S_,
                                                                 SegTiles st, void* out) {
   const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
-  if (g.ntiles > st.cap) return;  // the tile pass folded every segment whole
-  const Acc* first = static_cast<const Acc*>(st.first);
-  const Acc* last = static_cast<const Acc*>(st.last);
+  if (g.ntiles > st.cap || g.ntiles == 0) return;  // the tile pass folded every segment whole
   constexpr bool kComp = std::is_same_v<Acc, CompAcc>;
   // part k of a segment whose first tile is ts
-  auto part = [&](int64_t ts, int64_t k) { return k == 0 ? last[ts] : first[ts + k]; };
+  auto part = [&](int64_t ts, int64_t k) {
+    return word_acc<Acc>(k == 0 ? st.last[ts] : st.first[ts + k]);
+  };
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -849,7 +1176,7 @@ __global__ __launch_bounds__(256) void seg_tiles_combine_kernel(const elem_t<S>*
     if (j < S_) {
       const int64_t s = off[j] - g.lo, e = off[j + 1] - g.lo;
       if (e <= s) {
-        store_result<Acc>(out, j, Acc::zero());
+        store_result<Acc>(out, j, Acc::zero());  // empty (the pass without the scan leaves it)
       } else {
         ts = tile_of<S>(g, st.tile_vecs, s);
         te = tile_of<S>(g, st.tile_vecs, e - 1);

@@ -163,12 +163,11 @@ def make_functor(spec) -> Functor:
         if isinstance(a, int) and isinstance(b, int):
             f.ia, f.ib = a, b
     elif spec["fn"] == "horner":
-        c = list(spec["coef"])
+        c = [float(v) for v in spec["coef"]]
         if not 1 <= len(c) <= MAX_DEGREE + 1:
             raise ValueError(f"horner needs 1..{MAX_DEGREE + 1} coefficients")
         f.degree = len(c) - 1
-        for k, v in enumerate(c):
-            f.coef[k] = float(v)
+        f.coef[:len(c)] = c
     return f
 
 
@@ -176,12 +175,19 @@ def make_functor(spec) -> Functor:
 # Marshalling helpers
 # ---------------------------------------------------------------------------
 
+# The handle of a device's current stream.  The Stream object that
+# current_stream() builds around it costs 2 us, a quarter of a small call
+# (map of 4097 f32: 7.5 -> 4.9 us a call with the rest of this marshalling).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream(t: torch.Tensor) -> int:
-    return torch.cuda.current_stream(t.device).cuda_stream
+    return _raw_stream(t.get_device())
 
 
 def _gpu_tensor(t: torch.Tensor, name: str) -> torch.Tensor:
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
@@ -328,19 +334,19 @@ def batch_map_reduce(xs, map_fn, reduce_fn, acc="plain", ys=None, outs=None, ws=
         ys = [torch.empty_like(x) for x in xs] if map_fn is not None else [None] * len(xs)
     if outs is None:
         outs = [torch.empty((), dtype=OUT_DTYPE[a], device=dev) for _ in xs]
-    table = (BatchCall * len(xs))()
+    # the call table as one run of 64-bit words (x, y, n, out per call), filled at once
+    words = []
+    xdt, maps = xs[0].dtype, map_fn is not None
     for i, x in enumerate(xs):
         _gpu_tensor(x, "x")
-        if _dtype(x) != dt:
+        if x.dtype is not xdt:
             raise ValueError("all calls of a batch share one dtype")
         y = ys[i]
-        table[i].x = x.data_ptr()
-        table[i].y = y.data_ptr() if (y is not None and map_fn is not None) else None
-        table[i].n = x.numel()
-        table[i].out = outs[i].data_ptr()
+        words += (x.data_ptr(), y.data_ptr() if maps and y is not None else 0, x.numel(), outs[i].data_ptr())
+    table = (BatchCall * len(xs)).from_buffer((ctypes.c_uint64 * len(words))(*words))
     if ws is None:
         ws = workspace(dev, OP_BATCH, dt, a, sum(x.numel() for x in xs), len(xs))
-    f = ctypes.byref(make_functor(map_fn)) if map_fn is not None else None
+    f = ctypes.byref(make_functor(map_fn)) if maps else None
     g = make_functor(reduce_fn)
     _check(lib().hdc_batch_map_reduce(f, ctypes.byref(g), dt, a, table, len(xs), ws.data_ptr(), ws.numel(),
                                       _stream(xs[0])))

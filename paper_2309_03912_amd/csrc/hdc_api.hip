@@ -191,10 +191,14 @@ bool tune_cache_on() {
 void ensure_tuning_loaded() {
   std::call_once(g_tune_once, [] {
     // defaults that differ from the struct's: scans use 1024-thread tiles
-    // (16384 elements), so one block scans the tile sums of 2^28 elements
+    // (16384 elements), so one block scans the tile sums of 2^28 elements;
+    // smaller ones below 2^20 elements, to occupy more of the chip (800,000
+    // f32: 7.9 us at 512 threads or more, 9.5 at 256; 30,000 f32 compensated:
+    // 7.3 at 256, 10.2 at 1024).  A tile costs ~12 ns of the ticket's time, so
+    // 1e8 f32 in 4096-element tiles take 325 us against 165.
     for (auto& per_dt : g_tune[HDC_OP_SCAN])
       for (auto& per_acc : per_dt)
-        for (Tuning& t : per_acc) t.block = 1024;
+        for (int b = 0; b < kBuckets; ++b) per_acc[b].block = b == 0 ? 256 : b == 1 ? 512 : 1024;
     // segmented reduces take the tiled schedule (2M bf16 elements in 41,000
     // segments: 13.1 us in one launch, 23.8 us in the planned schedule's five)
     for (auto& per_dt : g_tune[HDC_OP_SEGMENTED_REDUCE])
@@ -333,17 +337,22 @@ hdc_status scratch_address(void** out) {
 constexpr int kTicketSlots = 1 << 11;  // 4352 bytes each
 static __device__ __align__(256) uint32_t tickets[(size_t)kTicketSlots * kTicketWords];
 
+// Look-back slots of the single-pass scans of few tiles, for the first
+// kScanSlots of those keys (8 MiB); zero-initialized as the tickets are.
+constexpr int kScanSlots = 1 << 10;
+static __device__ __align__(256) uint64_t scan_slots[(size_t)kScanSlots * kScanSlotWords];
+
 struct TicketTable {
-  uint32_t* base = nullptr;  // device address of `tickets` on this device
+  uint32_t* base = nullptr;  // device addresses of `tickets` and `scan_slots` on this device
+  uint64_t* scan_base = nullptr;
   std::map<std::pair<const void*, hipStream_t>, int> slot;
 };
 std::mutex g_ticket_mu;
 TicketTable g_ticket_tables[kMaxDevices];
 
-// The ticket of workspace buffer `ws` and stream `st` on the current device,
-// or NULL when no slot is left.
-hdc_status ticket_for(const void* ws, hipStream_t st, uint32_t** out) {
-  *out = nullptr;
+// The slot number of workspace buffer `ws` and stream `st` on the current
+// device, or -1 when none is left, and the device's table.
+hdc_status slot_for(const void* ws, hipStream_t st, int* slot, const TicketTable** table) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail(HDC_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
@@ -351,19 +360,49 @@ hdc_status ticket_for(const void* ws, hipStream_t st, uint32_t** out) {
   std::lock_guard<std::mutex> g(g_ticket_mu);
   TicketTable& tt = g_ticket_tables[dev];
   if (!tt.base) {
-    void* p = nullptr;
+    void *p = nullptr, *q = nullptr;
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(tickets));
-    if (e != hipSuccess || !p) return fail(HDC_ERR_HIP, "hipGetSymbolAddress(tickets): %s", hipGetErrorString(e));
+    if (e == hipSuccess) e = hipGetSymbolAddress(&q, HIP_SYMBOL(scan_slots));
+    if (e != hipSuccess || !p || !q) return fail(HDC_ERR_HIP, "hipGetSymbolAddress(tickets): %s", hipGetErrorString(e));
+    tt.scan_base = static_cast<uint64_t*>(q);
     tt.base = static_cast<uint32_t*>(p);
   }
+  *table = &tt;
   const std::pair<const void*, hipStream_t> key{ws, st};
   auto it = tt.slot.find(key);
   if (it == tt.slot.end()) {
-    if (tt.slot.size() >= (size_t)kTicketSlots) return HDC_OK;
+    if (tt.slot.size() >= (size_t)kTicketSlots) {
+      *slot = -1;
+      return HDC_OK;
+    }
     it = tt.slot.emplace(key, (int)tt.slot.size()).first;
   }
-  *out = tt.base + (size_t)it->second * kTicketWords;
+  *slot = it->second;
   return HDC_OK;
+}
+
+// The ticket of workspace buffer `ws` and stream `st`, or NULL.
+hdc_status ticket_for(const void* ws, hipStream_t st, uint32_t** out) {
+  int slot = -1;
+  const TicketTable* tt = nullptr;
+  HDC_TRY(slot_for(ws, st, &slot, &tt));
+  *out = slot < 0 ? nullptr : tt->base + (size_t)slot * kTicketWords;
+  return HDC_OK;
+}
+
+// The look-back slot of workspace buffer `ws` and stream `st`, or NULL.
+hdc_status scan_slot_for(const void* ws, hipStream_t st, uint64_t** out) {
+  int slot = -1;
+  const TicketTable* tt = nullptr;
+  HDC_TRY(slot_for(ws, st, &slot, &tt));
+  *out = slot < 0 || slot >= kScanSlots ? nullptr : tt->scan_base + (size_t)slot * kScanSlotWords;
+  return HDC_OK;
+}
+
+// A single pass of 2 .. kScanSlotTiles tiles keeps its look-back nodes in a slot.
+bool scan_takes_slot(int64_t n, const Tuning& t) {
+  const int64_t tile = (int64_t)t.block * kScanE, tiles = (n + tile - 1) / tile;
+  return t.unroll != 1 && tiles > 1 && tiles <= kScanSlotTiles;
 }
 
 // ---------------------------------------------------------------------------
@@ -680,7 +719,9 @@ hdc_status hdc_scan(const hdc_functor* f, hdc_dtype dt, const void* x, void* y, 
   HDC_TRY(resolve_workspace(workspace, ws_bytes, scan_workspace_bytes(n), st, &ws));
   log_dispatch(exclusive ? "scan (exclusive)" : "scan (inclusive)", dt, acc, n, t,
                t.unroll == 1 ? "three passes" : "one pass (tree carry)", workspace ? "caller" : "library");
-  return run_scan(*f, dt, x, y, n, acc, exclusive, ws, t, st);
+  uint64_t* slot = nullptr;
+  if (scan_takes_slot(n, t)) HDC_TRY(scan_slot_for(ws, st, &slot));
+  return run_scan(*f, dt, x, y, n, acc, exclusive, ws, slot, t, st);
 }
 
 hdc_status hdc_segmented_scan(const hdc_functor* f, hdc_dtype dt, const void* x, const int64_t* offsets,
@@ -708,7 +749,9 @@ hdc_status hdc_segmented_scan(const hdc_functor* f, hdc_dtype dt, const void* x,
   HDC_TRY(resolve_workspace(workspace, ws_bytes, scan_workspace_bytes(total), st, &ws));
   log_dispatch(exclusive ? "segmented_scan (exclusive)" : "segmented_scan (inclusive)", dt, acc, total, t,
                t.unroll == 1 ? "three passes" : "one pass (tree carry)", workspace ? "caller" : "library");
-  return run_segmented_scan(*f, dt, x, offsets, num_segments, y, total, acc, exclusive, ws, t, st);
+  uint64_t* slot = nullptr;
+  if (scan_takes_slot(total, t)) HDC_TRY(scan_slot_for(ws, st, &slot));
+  return run_segmented_scan(*f, dt, x, offsets, num_segments, y, total, acc, exclusive, ws, slot, t, st);
 }
 
 hdc_status hdc_scan_status(const void* workspace, int32_t* status, void* stream) {

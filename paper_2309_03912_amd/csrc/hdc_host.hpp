@@ -243,11 +243,12 @@ hdc_status run_batch(const hdc_functor* fm, const hdc_functor& g, hdc_dtype dt, 
                      const hdc_batch_call* calls, const int32_t* idx, int cnt, void* ws, size_t ws_bytes,
                      const Tuning& t, hipStream_t st);
 
+// `slot`: see launch_scan; NULL: the look-back nodes go to the workspace.
 hdc_status run_scan(const hdc_functor& f, hdc_dtype dt, const void* x, void* y, int64_t n, hdc_accum acc,
-                    int exclusive, void* ws, const Tuning& t, hipStream_t st);
+                    int exclusive, void* ws, uint64_t* slot, const Tuning& t, hipStream_t st);
 hdc_status run_segmented_scan(const hdc_functor& f, hdc_dtype dt, const void* x, const int64_t* off,
                               int64_t nseg, void* y, int64_t n, hdc_accum acc, int exclusive, void* ws,
-                              const Tuning& t, hipStream_t st);
+                              uint64_t* slot, const Tuning& t, hipStream_t st);
 // Workspace of a scan (also segmented), for tiles of at least 64 * 16
 // elements: a 256-byte header (the status word at byte 4), then the larger
 // of the three-pass need (tile sums and offsets, at most 16 bytes each per

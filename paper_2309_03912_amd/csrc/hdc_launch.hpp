@@ -323,9 +323,11 @@ hdc_status launch_batch(const FM& fm, bool maps, const F& f, const hdc_batch_cal
 //                 fold state per tile each;
 //   single pass:  256-byte header (ticket, status) | the tree nodes
 //                 (tree_nodes(G), level by level), kWords 8-byte words each.
+// `slot`: kScanSlotWords words of library memory for a single pass of at most
+// kScanSlotTiles tiles, or NULL.
 template <class F, class S, class Acc>
 hdc_status launch_scan(const F& f, const void* x, void* y, int64_t n, int exclusive, SegSpec seg, void* ws,
-                       const Tuning& t, hipStream_t st) {
+                       uint64_t* slot, const Tuning& t, hipStream_t st) {
   using T = typename S::T;
   using OutT = typename ScanOut<Acc>::T;
   static_assert(sizeof(Acc) <= 24, "scan_workspace_bytes holds 24 bytes per tile and array");
@@ -338,12 +340,21 @@ hdc_status launch_scan(const F& f, const void* x, void* y, int64_t n, int exclus
   OutT* yp = static_cast<OutT*>(y);
   const dim3 grid((unsigned)G), block(t.block);
   if (t.unroll != 1) {
+    // The look-back nodes: none for one tile, a library slot for few, else the
+    // workspace, cleared first.  (The clear is a launch of its own, ~4 us of the
+    // host's time: 12.3 us a call for 112,000 f32 with it.)
     uint64_t* w = static_cast<uint64_t*>(ws);
-    const int64_t nwords = 32 + (int64_t)ScanCarry<Acc>::kWords * tree_nodes(G);
-    const ScanLB lb{static_cast<uint32_t*>(ws), static_cast<uint32_t*>(ws) + 1, w + 32};
-    const int64_t cb = (nwords + 255) / 256;
-    scan_lb_clear_kernel<<<dim3((unsigned)(cb < 1024 ? cb : 1024)), dim3(256), 0, st>>>(w, nwords);
-    HDC_TRY(check_launch("scan look-back clear launch"));
+    uint32_t* const status = static_cast<uint32_t*>(ws) + 1;
+    ScanLB lb{static_cast<uint32_t*>(ws), nullptr, status, w + 32, 1};
+    if (G > 1 && G <= kScanSlotTiles && slot) {
+      lb.ticket64 = slot;
+      lb.node = slot + 16;
+    } else if (G > 1) {
+      const int64_t nwords = 32 + (int64_t)ScanCarry<Acc>::kWords * tree_nodes(G);
+      const int64_t cb = (nwords + 255) / 256;
+      scan_lb_clear_kernel<<<dim3((unsigned)(cb < 1024 ? cb : 1024)), dim3(256), 0, st>>>(w, nwords);
+      HDC_TRY(check_launch("scan look-back clear launch"));
+    }
     if (sizeof(T) == 4 || even)
       scan_onepass_kernel<F, S, Acc, true><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
     else if constexpr (sizeof(T) < 4)

@@ -674,16 +674,35 @@ struct ScanCarry<SegAcc<Acc>> {
   __device__ static T unpack(const uint32_t* w) { return {B::unpack(w), w[2]}; }
 };
 
-// Look-back state in the workspace: the tree nodes (tree_nodes(tiles) of
-// them, level by level), kWords 64-bit words each.  Every word holds one 32-bit part of the value below a
-// ready flag (bit 32), so it is written and read by one single-copy-atomic
-// access and no fence orders a value against a separate flag.  All words
-// start at zero (scan_lb_clear_kernel runs first on the same stream).
+// Look-back state: the tree nodes (tree_nodes(tiles) of them, level by level),
+// kWords 64-bit words each.  Every word holds one 32-bit part of the value
+// below a 32-bit tag, so it is written and read by one single-copy-atomic
+// access and no fence orders a value against a separate flag; a word is ready
+// when its tag is the launch's.  Two places for them:
+//  * the workspace, whose words scan_lb_clear_kernel sets to zero first, on
+//    the same stream; the tag is 1;
+//  * for up to kScanSlotTiles tiles a slot of library-owned memory (one per
+//    workspace and stream, zero when the library is loaded), with no clear
+//    launch: the slot's ticket carries a launch epoch in its upper half, which
+//    the block that draws the last tile moves on, and the tag is the epoch +
+//    1.  Only these kernels write a slot, so a word of an earlier launch has
+//    an earlier tag (until it would repeat, after 2^32 launches).
 struct ScanLB {
-  uint32_t* ticket;  // next tile to hand out
-  uint32_t* status;  // nonzero: a wait gave up (the result is invalid)
-  uint64_t* node;    // level 0 (one node per tile), then levels 1, 2, ...
+  uint32_t* ticket;   // next tile to hand out (workspace)
+  uint64_t* ticket64; // epoch and next tile (slot), or NULL
+  uint32_t* status;   // nonzero: a wait gave up (the result is invalid)
+  uint64_t* node;     // level 0 (one node per tile), then levels 1, 2, ...
+  uint32_t tag;       // set by the kernel
 };
+
+constexpr int64_t kScanSlotTiles = 256;
+constexpr int64_t kScanSlotWords = 16 + 3 * (kScanSlotTiles + kScanSlotTiles / 64);  // the ticket's line, the nodes
+
+// What a slot launch that gave up leaves in the status word (its own mark, so
+// that the first tile can clear an earlier call's word at any time).
+__device__ __forceinline__ uint32_t gave_up_mark(const ScanLB& lb) {
+  return lb.ticket64 ? (lb.tag * 2654435761u) | 1u : 1u;
+}
 
 constexpr uint32_t kLookbackSpinLimit = 1u << 16;  // polls before giving up
 
@@ -693,22 +712,10 @@ static __global__ __launch_bounds__(256) void scan_lb_clear_kernel(uint64_t* w, 
 }
 
 template <int W>
-__device__ __forceinline__ void lb_publish(uint64_t* node, const uint32_t (&v)[W]) {
+__device__ __forceinline__ void lb_publish(uint64_t* node, uint32_t tag, const uint32_t (&v)[W]) {
 #pragma unroll
   for (int k = 0; k < W; ++k)
-    __hip_atomic_store(node + k, (uint64_t(1) << 32) | v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <int W>
-__device__ __forceinline__ bool lb_read(const uint64_t* node, uint32_t (&v)[W]) {
-  bool ok = true;
-#pragma unroll
-  for (int k = 0; k < W; ++k) {
-    const uint64_t w = __hip_atomic_load(node + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v[k] = (uint32_t)w;
-    ok = ok && (w >> 32) != 0;
-  }
-  return ok;
+    __hip_atomic_store(node + k, ((uint64_t)tag << 32) | v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The carry between tiles as a tree of radix 64 over the tile totals.  A
@@ -790,7 +797,7 @@ __device__ typename C::T scan_tree_carry(const ScanLB& lb, int64_t t, int64_t ti
   auto publish = [&](int k, T x) {
     uint32_t w[W];
     C::pack(x, w);
-    if (lane == 0) lb_publish<W>(lb.node + start(k) + (int64_t)W * (t >> (6 * k)), w);
+    if (lane == 0) lb_publish<W>(lb.node + start(k) + (int64_t)W * (t >> (6 * k)), lb.tag, w);
   };
   publish(0, own);
   int P = 0;  // group nodes this tile owes: levels 1 .. P
@@ -826,7 +833,7 @@ __device__ typename C::T scan_tree_carry(const ScanLB& lb, int64_t t, int64_t ti
         if (k < K && ((pend >> k) & 1u)) {
           bool ok = true;
 #pragma unroll
-          for (int i = 0; i < W; ++i) ok = ok && (got[b][i] >> 32) != 0;
+          for (int i = 0; i < W; ++i) ok = ok && (uint32_t)(got[b][i] >> 32) == lb.tag;
           if (ok) {
 #pragma unroll
             for (int i = 0; i < W; ++i) slots[(k * W + i) * 64 + lane] = (uint32_t)got[b][i];
@@ -846,7 +853,7 @@ __device__ typename C::T scan_tree_carry(const ScanLB& lb, int64_t t, int64_t ti
   }
   if (!all) {  // gave up: keep the others moving, flag the result
     for (; pub < P; ++pub) publish(pub + 1, own);
-    if (lane == 0) __hip_atomic_store(lb.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) __hip_atomic_store(lb.status, gave_up_mark(lb), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return C::zero();
   }
   T carry = C::zero();
@@ -879,6 +886,7 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   using C = ScanCarry<Acc>;
   __shared__ Acc lds[kMaxWaves];
   __shared__ int64_t tile_sh;
+  __shared__ uint32_t tag_sh;
   __shared__ typename C::T carry_sh;
   __shared__ uint32_t slots[kTreeLevels * C::kWords * 64];
   __shared__ uint32_t heads_sh[IsSeg<Acc>::value ? kTileWords : 1];
@@ -889,9 +897,33 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   // go out with the ticket.
   HeadProbe pr{0, 0};
   if constexpr (IsSeg<Acc>::value) pr = heads_probe(seg);
-  if (threadIdx.x == 0) tile_sh = (int64_t)atomicAdd(lb.ticket, 1u);
+  const bool only = gridDim.x == 1;  // one tile: no ticket, no carry
+  if (threadIdx.x == 0) {
+    uint32_t t = 0;
+    lb.tag = 1;
+    if (only) {
+      *lb.status = 0;
+    } else if (!lb.ticket64) {
+      t = atomicAdd(lb.ticket, 1u);
+    } else {
+      const uint64_t old = __hip_atomic_fetch_add(lb.ticket64, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      t = (uint32_t)old;
+      lb.tag = (uint32_t)(old >> 32) + 1;
+      if (t == gridDim.x - 1)  // every tile is drawn: the next epoch, from tile 0
+        __hip_atomic_fetch_add(lb.ticket64, (1ull << 32) - gridDim.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (t == 0) {  // an earlier call's status goes; this call's mark (a later tile gave up already) stays
+        uint32_t st = __hip_atomic_load(lb.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (st != 0 && st != gave_up_mark(lb))
+          __hip_atomic_compare_exchange_strong(lb.status, &st, 0u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    tile_sh = (int64_t)t;
+    tag_sh = lb.tag;
+  }
   __syncthreads();
   const int64_t tile = tile_sh;
+  lb.tag = tag_sh;
   auto w = scan_wave_at<F, S, Acc>(tile, n);
   w.template load<kEven>(x, seg);
   if constexpr (IsSeg<Acc>::value)
@@ -899,7 +931,9 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   w.fold(f);
   Acc total;
   const Acc before = block_wave_prefix(w.wave_total, lds, &total);
-  if (threadIdx.x < 64) {
+  if (only) {
+    if (threadIdx.x == 0) carry_sh = C::zero();
+  } else if (threadIdx.x < 64) {
     // Segmented scans park wavefront 0's lane state in LDS while it polls:
     // the polls and the lane state together needed ~70 VGPRs, over the 64
     // that two 1024-thread blocks per CU allow.

@@ -358,7 +358,8 @@ struct ScanWave {
   // when a lane's run is exactly 16 bytes, so a wavefront's store covers whole
   // lines; cached otherwise, so the cache merges the interleaved runs of a
   // chunk into whole lines).
-  // With 32 output bytes per lane and chunk (V = 2 PER), a whole chunk goes
+  // With 32 output bytes per lane and chunk (V = 2 PER; with 64, V = 4 PER,
+  // half a wavefront at a time), a whole chunk goes
   // through the wavefront's 2 KiB `stage` (LDS): each lane writes its 32
   // bytes, then takes the 16-byte pieces at lanes l and 64 + l of the
   // chunk's output, so that each non-temporal store instruction of the
@@ -391,6 +392,25 @@ struct ScanWave {
           u32x4_word* p = reinterpret_cast<u32x4_word*>(y + index(q, 0) - (int64_t)lane * V);  // the chunk's start
           __builtin_nontemporal_store(r0, p + lane);
           __builtin_nontemporal_store(r1, p + 64 + lane);
+        } else if constexpr (V == 4 * PER) {
+          // 64 bytes per lane: the lower 32 lanes' 2 KiB, then the upper ones'
+          u32x4_word* p = reinterpret_cast<u32x4_word*>(y + index(q, 0) - (int64_t)lane * V);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            if ((lane >> 5) == h) {
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                u32x4 w;
+                __builtin_memcpy(&w, &o[k * PER], 16);
+                stage[4 * (lane & 31) + k] = w;
+              }
+            }
+            __builtin_amdgcn_wave_barrier();
+            const u32x4 r0 = stage[lane], r1 = stage[64 + lane];
+            __builtin_amdgcn_wave_barrier();
+            __builtin_nontemporal_store(r0, p + h * 128 + lane);
+            __builtin_nontemporal_store(r1, p + h * 128 + 64 + lane);
+          }
         } else {
 #pragma unroll
           for (int h = 0; h < V / PER; ++h) {
@@ -455,10 +475,10 @@ __device__ __forceinline__ ScanWave<F, S, Acc> scan_wave_at(int64_t tile, int64_
 constexpr int kTileWords = 1024 * kScanE / 32;  // bitmap words of the largest tile
 
 // 16-byte vectors of output staging per block: 2 KiB per wavefront when a
-// lane's outputs of a chunk are 32 bytes, none otherwise.
+// lane's outputs of a chunk are 32 or 64 bytes, none otherwise.
 template <class S, class Acc>
 constexpr int kStageVecs =
-    S::kVec * sizeof(typename ScanOut<Acc>::T) == 32 ? kMaxWaves * 128 : 1;
+    S::kVec * sizeof(typename ScanOut<Acc>::T) >= 32 ? kMaxWaves * 128 : 1;
 
 // This thread's probe for the first round: offset (tid + 1) step - 1 of the
 // m offsets (clamped to the last one), step = ceil(m / blockDim).  With m no
@@ -808,6 +828,7 @@ __device__ typename C::T scan_tree_carry(const ScanLB& lb, int64_t t, int64_t ti
   T up = own;  // this tile's node at level `pub`
   int pub = 0;
   bool all = false;
+  int top = K;  // levels from `top` on lie before a segment start
   for (uint32_t polls = 0;; ++polls) {
     // Levels in groups of kBatch: the reads of a group are all issued before
     // any of them is examined, so a poll of K <= kBatch levels costs one round
@@ -842,12 +863,36 @@ __device__ typename C::T scan_tree_carry(const ScanLB& lb, int64_t t, int64_t ti
         }
       }
     }
+    // Can the fold of level k's lanes 0 .. m-1 be taken?  Its nodes are all in,
+    // or (segmented) a node holding a segment start is in and so is every node
+    // after it: what lies before the start does not count.  `cut`: it is such a
+    // start that decides.
+    auto known = [&](int k, int m, bool& cut) {
+      const uint64_t wait = __builtin_amdgcn_ballot_w64((pend >> k) & 1u);
+      cut = false;
+      if constexpr (W == 3) {
+        const bool in = lane < m && !((pend >> k) & 1u);
+        const uint64_t starts = __builtin_amdgcn_ballot_w64(in && slots[(k * W + 2) * 64 + lane] != 0);
+        cut = starts > wait;  // the last start comes after every node that is missing
+      }
+      return cut || wait == 0;
+    };
+    bool cut;
     for (; pub < P; ++pub) {
-      if (__builtin_amdgcn_ballot_w64((pend >> pub) & 1u) != 0) break;
+      if (!known(pub, 63, cut)) break;
       up = C::add(wave_ordered_fold<C>(slots + pub * W * 64, 63), up);
       publish(pub + 1, up);
     }
-    all = __builtin_amdgcn_ballot_w64(pend != 0) == 0;
+    all = pub == P;
+    top = K;
+    for (int k = 0; all && k < K; ++k) {
+      if (digit(k) == 0) continue;
+      all = known(k, digit(k), cut);
+      if (cut) {
+        top = k + 1;
+        break;
+      }
+    }
     if (all || polls >= kLookbackSpinLimit) break;
     __builtin_amdgcn_s_sleep(1);
   }
@@ -858,7 +903,7 @@ __device__ typename C::T scan_tree_carry(const ScanLB& lb, int64_t t, int64_t ti
   }
   T carry = C::zero();
   bool any = false;
-  for (int k = K - 1; k >= 0; --k) {
+  for (int k = top - 1; k >= 0; --k) {
     const int m = digit(k);
     if (m == 0) continue;
     const T f = wave_ordered_fold<C>(slots + k * W * 64, m);
@@ -877,6 +922,10 @@ template <class Acc>
 struct OnepassWaves : std::integral_constant<int, 1> {};
 template <>
 struct OnepassWaves<SegAcc<PlainAcc>> : std::integral_constant<int, 8> {};
+template <>
+struct OnepassWaves<SegAcc<IntAcc>> : std::integral_constant<int, 8> {};
+template <>
+struct OnepassWaves<IntAcc> : std::integral_constant<int, 8> {};
 
 template <class F, class S, class Acc, bool kEven>
   requires device_callable<F>
@@ -885,14 +934,15 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
                                                             ScanLB lb, typename ScanOut<Acc>::T* y, int exclusive) {
   using C = ScanCarry<Acc>;
   __shared__ Acc lds[kMaxWaves];
-  __shared__ int64_t tile_sh;
+  __shared__ uint32_t tile_sh;
   __shared__ uint32_t tag_sh;
   __shared__ typename C::T carry_sh;
   __shared__ uint32_t slots[kTreeLevels * C::kWords * 64];
   __shared__ uint32_t heads_sh[IsSeg<Acc>::value ? kTileWords : 1];
   __shared__ uint32_t wfirst_sh[kMaxWaves];
   __shared__ u32x4 stage_sh[kStageVecs<S, Acc>];
-  __shared__ uint32_t park_sh[IsSeg<Acc>::value ? ScanWave<F, S, Acc>::kStashWords * 64 : 1];
+  constexpr bool kPark = IsSeg<Acc>::value || std::is_same_v<Acc, IntAcc>;
+  __shared__ uint32_t park_sh[kPark ? ScanWave<F, S, Acc>::kStashWords * 64 : 1];
   // The probes of the segment-start search do not depend on the tile: they
   // go out with the ticket.
   HeadProbe pr{0, 0};
@@ -918,12 +968,12 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
                                                __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    tile_sh = (int64_t)t;
+    tile_sh = t;
     tag_sh = lb.tag;
   }
   __syncthreads();
-  const int64_t tile = tile_sh;
-  lb.tag = tag_sh;
+  const int64_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)tile_sh);
+  lb.tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)tag_sh);
   auto w = scan_wave_at<F, S, Acc>(tile, n);
   w.template load<kEven>(x, seg);
   if constexpr (IsSeg<Acc>::value)
@@ -931,16 +981,15 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   w.fold(f);
   Acc total;
   const Acc before = block_wave_prefix(w.wave_total, lds, &total);
-  if (only) {
-    if (threadIdx.x == 0) carry_sh = C::zero();
-  } else if (threadIdx.x < 64) {
+  if (threadIdx.x < 64) {
     // Segmented scans park wavefront 0's lane state in LDS while it polls:
     // the polls and the lane state together needed ~70 VGPRs, over the 64
     // that two 1024-thread blocks per CU allow.
-    if constexpr (IsSeg<Acc>::value) w.stash(park_sh);
-    const typename C::T carry = scan_tree_carry<C>(lb, tile, (int64_t)gridDim.x, C::of(total), slots);
+    if constexpr (kPark) w.stash(park_sh);
+    typename C::T carry = C::zero();
+    if (!only) carry = scan_tree_carry<C>(lb, tile, (int64_t)gridDim.x, C::of(total), slots);
     if (threadIdx.x == 0) carry_sh = carry;
-    if constexpr (IsSeg<Acc>::value) w.unstash(park_sh);
+    if constexpr (kPark) w.unstash(park_sh);
   }
   __syncthreads();
   w.emit(f, Acc::merge(C::to(carry_sh), before), exclusive, y,

@@ -331,11 +331,14 @@ hdc_status launch_scan(const F& f, const void* x, void* y, int64_t n, int exclus
   using T = typename S::T;
   using OutT = typename ScanOut<Acc>::T;
   static_assert(sizeof(Acc) <= 24, "scan_workspace_bytes holds 24 bytes per tile and array");
-  const int64_t tile = (int64_t)t.block * kScanE;
-  const int64_t G = (n + tile - 1) / tile;
-  if (G * t.block > (int64_t)UINT32_MAX) return fail(HDC_ERR_UNSUPPORTED, "n = %lld is too large for one scan", (long long)n);
+  const int64_t narrow = (int64_t)t.block * kScanE;
+  if ((n + narrow - 1) / narrow * t.block > (int64_t)UINT32_MAX)
+    return fail(HDC_ERR_UNSUPPORTED, "n = %lld is too large for one scan", (long long)n);
   // 2-byte storage that does not start on 4-byte boundaries takes global loads
   const bool even = (uintptr_t)x % 4 == 0;
+  const bool wide = ScanWide<Acc>::value && t.unroll != 1 && n >= kScanWideN && (sizeof(T) == 4 || even);
+  const int64_t tile = wide ? 2 * narrow : narrow;
+  const int64_t G = (n + tile - 1) / tile;
   const T* xp = static_cast<const T*>(x);
   OutT* yp = static_cast<OutT*>(y);
   const dim3 grid((unsigned)G), block(t.block);
@@ -355,10 +358,14 @@ hdc_status launch_scan(const F& f, const void* x, void* y, int64_t n, int exclus
       scan_lb_clear_kernel<<<dim3((unsigned)(cb < 1024 ? cb : 1024)), dim3(256), 0, st>>>(w, nwords);
       HDC_TRY(check_launch("scan look-back clear launch"));
     }
-    if (sizeof(T) == 4 || even)
-      scan_onepass_kernel<F, S, Acc, true><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
-    else if constexpr (sizeof(T) < 4)
-      scan_onepass_kernel<F, S, Acc, false><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
+    if (wide) {
+      if constexpr (ScanWide<Acc>::value)
+        scan_onepass_kernel<F, S, Acc, 2 * kScanE, true><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
+    } else if (sizeof(T) == 4 || even) {
+      scan_onepass_kernel<F, S, Acc, kScanE, true><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
+    } else if constexpr (sizeof(T) < 4) {
+      scan_onepass_kernel<F, S, Acc, kScanE, false><<<grid, block, 0, st>>>(f, xp, n, seg, lb, yp, exclusive);
+    }
     return check_launch("scan single-pass launch");
   }
   // three passes: the same 256-byte header (its status word cleared by the

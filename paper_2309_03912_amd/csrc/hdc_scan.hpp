@@ -1,8 +1,9 @@
 // Prefix sums of f(x): y[i] = fold of f(x[0..i]) (inclusive) or f(x[0..i-1])
-// (exclusive), over tiles of T = blockDim * kScanE elements.
+// (exclusive), over tiles of T = blockDim * E elements,
+// E = kScanE, or 2 kScanE (ScanWide).
 //
-// Layout of a tile: wavefront w owns the 64 * kScanE contiguous elements
-// starting at w * 64 * kScanE, as Q = kScanE / V chunks of 64 * V elements
+// Layout of a tile: wavefront w owns the 64 * E contiguous elements
+// starting at w * 64 * E, as Q = E / V chunks of 64 * V elements
 // (V = elements per 16-byte vector).  In chunk q, lane l owns the V elements
 // at q * 64 V + l V: every load of a wavefront covers one contiguous 1-KiB
 // span, and so does every store when a lane's outputs of a chunk take 16
@@ -35,6 +36,7 @@
 namespace hdc {
 
 constexpr int kScanE = 16;  // elements per thread per tile
+
 
 template <class T>
 __device__ __forceinline__ T shfl_up_words(T v, int d) {
@@ -189,18 +191,18 @@ struct SegSpec {
 // each lane takes the segment-start bits of its elements from the tile's
 // bitmap (tile_heads) into `hmask`; outputs are written only inside
 // [off[0], off[S]).
-template <class F, class S, class Acc>
+template <class F, class S, class Acc, int E>
 struct ScanWave {
   static constexpr int V = S::kVec;
-  static constexpr int Q = kScanE / V;
+  static constexpr int Q = E / V;
   static constexpr bool kSeg = IsSeg<Acc>::value;
   using OutT = typename ScanOut<Acc>::T;
 
   int64_t wbase;  // first element of this wavefront's part
   int lane;
   int64_t n;
-  elem_t<S> v[kScanE];             // chunk q, element e at v[q V + e]
-  [[maybe_unused]] float t[kScanE];  // the terms (floats)
+  elem_t<S> v[E];             // chunk q, element e at v[q V + e]
+  [[maybe_unused]] float t[E];  // the terms (floats)
   Acc ex[Q];                       // exclusive prefix of this lane within chunk q
   Acc wc[Q];                       // fold of chunks 0..q-1 of this wavefront
   Acc wave_total;
@@ -212,14 +214,14 @@ struct ScanWave {
   // kEven: x starts on a 4-byte boundary, as buffer loads need.
   template <bool kEven>
   __device__ void load(const elem_t<S>* x, const SegSpec& seg) {
-    if (wbase + 64 * kScanE <= n) {
+    if (wbase + 64 * E <= n) {
       Vec<S> a[Q];
       if constexpr (kEven) {
         // a raw buffer resource over this wavefront's part (word 3 0x00020000:
         // 32-bit data format, no swizzle; cache policy 2: non-temporal), so the
         // lane offsets stay fixed instead of 64-bit address arithmetic per load
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-            (void*)(x + wbase), (short)0, (int)(64 * kScanE * sizeof(elem_t<S>)), 0x00020000);
+            (void*)(x + wbase), (short)0, (int)(64 * E * sizeof(elem_t<S>)), 0x00020000);
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
           const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rx, (uint32_t)(q * 64 + lane) * 16u, 0, 2);
@@ -263,7 +265,7 @@ struct ScanWave {
   // The lane state that emit needs, as 32-bit words: the terms (float
   // storage) or the elements (int32), the chunk prefixes and the heads.
   static constexpr int kStashWords =
-      kScanE + Q * (int)(sizeof(Acc) / 4) + (kSeg ? 1 : 0);
+      E + Q * (int)(sizeof(Acc) / 4) + (kSeg ? 1 : 0);
   // Park that state in LDS (word c of lane l at s[c * 64 + l]) and take it
   // back: a wavefront that runs the carry's polls between the two holds none
   // of it in registers meanwhile.
@@ -331,7 +333,7 @@ struct ScanWave {
     Acc tot[Q];
     if constexpr (!std::is_same_v<S, I32>) {
 #pragma unroll
-      for (int k = 0; k < kScanE; ++k) t[k] = S::widen(v[k]);
+      for (int k = 0; k < E; ++k) t[k] = S::widen(v[k]);
       eval_batch(f, t);  // once: the terms serve the totals and the outputs
     }
 #pragma unroll
@@ -367,8 +369,8 @@ struct ScanWave {
   __device__ void emit(const F& f, const Acc& before, int exclusive, OutT* y, u32x4* stage) const {
     constexpr int PER = 16 / sizeof(OutT);
     // y needs its element's alignment only: the same 16-byte stores serve every address
-    bool full = wbase + 64 * kScanE <= n;
-    if constexpr (kSeg) full = full && wbase >= out_lo && wbase + 64 * kScanE <= out_hi;
+    bool full = wbase + 64 * E <= n;
+    if constexpr (kSeg) full = full && wbase >= out_lo && wbase + 64 * E <= out_hi;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       Acc a = Acc::merge(Acc::merge(before, wc[q]), ex[q]);
@@ -454,11 +456,11 @@ __device__ __forceinline__ Acc block_wave_prefix(const Acc& wave_total, Acc* lds
   return wid > 0 ? prev : Acc::zero();
 }
 
-template <class F, class S, class Acc>
-__device__ __forceinline__ ScanWave<F, S, Acc> scan_wave_at(int64_t tile, int64_t n) {
-  ScanWave<F, S, Acc> w;
+template <class F, class S, class Acc, int E = kScanE>
+__device__ __forceinline__ ScanWave<F, S, Acc, E> scan_wave_at(int64_t tile, int64_t n) {
+  ScanWave<F, S, Acc, E> w;
   w.lane = threadIdx.x & 63;
-  w.wbase = tile * (int64_t)blockDim.x * kScanE + (int64_t)(threadIdx.x >> 6) * 64 * kScanE;
+  w.wbase = tile * (int64_t)blockDim.x * E + (int64_t)(threadIdx.x >> 6) * 64 * E;
   w.n = n;
   return w;
 }
@@ -472,7 +474,8 @@ __device__ __forceinline__ ScanWave<F, S, Acc> scan_wave_at(int64_t tile, int64_
 // that gap until they pass the tile.  Then each wavefront takes its lanes'
 // bits (ScanWave::take_heads).  Empty segments repeat a boundary, which sets
 // the same bit again.
-constexpr int kTileWords = 1024 * kScanE / 32;  // bitmap words of the largest tile
+template <int E>
+constexpr int kTileWords = 1024 * E / 32;  // bitmap words of the largest tile
 
 // 16-byte vectors of output staging per block: 2 KiB per wavefront when a
 // lane's outputs of a chunk are 32 or 64 bytes, none otherwise.
@@ -538,7 +541,7 @@ template <class F, class S, class Acc, bool kEven>
 __global__ __launch_bounds__(1024) void scan_tile_sums_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
                                                               Acc* sums) {
   __shared__ Acc lds[kMaxWaves];
-  __shared__ uint32_t heads_sh[IsSeg<Acc>::value ? kTileWords : 1];
+  __shared__ uint32_t heads_sh[IsSeg<Acc>::value ? kTileWords<kScanE> : 1];
   __shared__ uint32_t wfirst_sh[kMaxWaves];
   auto w = scan_wave_at<F, S, Acc>(blockIdx.x, n);
   HeadProbe pr{0, 0};
@@ -601,7 +604,7 @@ __global__ __launch_bounds__(1024) void scan_tiles_kernel(F f, const elem_t<S>* 
                                                           const Acc* offsets, typename ScanOut<Acc>::T* y,
                                                           int exclusive) {
   __shared__ Acc lds[kMaxWaves];
-  __shared__ uint32_t heads_sh[IsSeg<Acc>::value ? kTileWords : 1];
+  __shared__ uint32_t heads_sh[IsSeg<Acc>::value ? kTileWords<kScanE> : 1];
   __shared__ uint32_t wfirst_sh[kMaxWaves];
   __shared__ u32x4 stage_sh[kStageVecs<S, Acc>];
   auto w = scan_wave_at<F, S, Acc>(blockIdx.x, n);
@@ -913,23 +916,39 @@ __device__ typename C::T scan_tree_carry(const ScanLB& lb, int64_t t, int64_t ti
   return carry;
 }
 
-// One tile per block; the tile index comes from the ticket, not blockIdx.
+// The folds whose single pass takes tiles of 2 kScanE elements per thread from
+// kScanWideN elements on.  What bounds a long scan is the tiles' common work
+// (ticket, node, polls: ~12 ns per tile on the whole card), so half the tiles
+// help as long as their lane state stays in registers: it does for one double
+// or one int64 per element, not for a double-double (f32 compensated 323 us ->
+// 345 at 1.34e8) or with segment starts (int64 328 -> 522).  Plain and int64,
+// 2 kScanE / kScanE at 1024 threads, us:
+//   n       f32 plain    bf16 plain     i32
+//   1.7e7  42.6 / 38.8  38.0 / 39.7  51.1 / 49.7
+//   4e7    74.2 / 74.8  65.2 / 77.6  96.6 / 98.4
+//   1.34e8  209 / 215    185 / 235    279 / 293
+template <class Acc>
+struct ScanWide : std::bool_constant<std::is_same_v<Acc, PlainAcc> || std::is_same_v<Acc, IntAcc>> {};
+constexpr int64_t kScanWideN = int64_t(1) << 25;
+
 // Waves per SIMD the single-pass kernel is compiled for (1: the compiler's
 // choice).  The plain segmented scan needs a few VGPRs over 64; holding it to
 // 64 (two 1024-thread blocks per CU) spills 32 bytes per lane and still runs
-// 18% faster.  The int64 scans would spill ~100 bytes per lane and slow down.
-template <class Acc>
-struct OnepassWaves : std::integral_constant<int, 1> {};
-template <>
-struct OnepassWaves<SegAcc<PlainAcc>> : std::integral_constant<int, 8> {};
-template <>
-struct OnepassWaves<SegAcc<IntAcc>> : std::integral_constant<int, 8> {};
-template <>
-struct OnepassWaves<IntAcc> : std::integral_constant<int, 8> {};
+// 18% faster.  The int64 scans would spill ~100 bytes per lane and slow down,
+// but with wavefront 0's lane state parked in LDS they fit.  A wide tile holds
+// twice the lane state: 6 waves, 80 VGPRs.
+template <class Acc, int E>
+struct OnepassWaves
+    : std::integral_constant<int, (E > kScanE) ? 6
+                                  : std::is_same_v<Acc, IntAcc> || std::is_same_v<Acc, SegAcc<PlainAcc>> ||
+                                          std::is_same_v<Acc, SegAcc<IntAcc>>
+                                      ? 8
+                                      : 1> {};
 
-template <class F, class S, class Acc, bool kEven>
+// One tile per block; the tile index comes from the ticket, not blockIdx.
+template <class F, class S, class Acc, int E, bool kEven>
   requires device_callable<F>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(OnepassWaves<Acc>::value))) void
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(OnepassWaves<Acc, E>::value))) void
 scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
                                                             ScanLB lb, typename ScanOut<Acc>::T* y, int exclusive) {
   using C = ScanCarry<Acc>;
@@ -938,11 +957,11 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   __shared__ uint32_t tag_sh;
   __shared__ typename C::T carry_sh;
   __shared__ uint32_t slots[kTreeLevels * C::kWords * 64];
-  __shared__ uint32_t heads_sh[IsSeg<Acc>::value ? kTileWords : 1];
+  __shared__ uint32_t heads_sh[IsSeg<Acc>::value ? kTileWords<E> : 1];
   __shared__ uint32_t wfirst_sh[kMaxWaves];
   __shared__ u32x4 stage_sh[kStageVecs<S, Acc>];
-  constexpr bool kPark = IsSeg<Acc>::value || std::is_same_v<Acc, IntAcc>;
-  __shared__ uint32_t park_sh[kPark ? ScanWave<F, S, Acc>::kStashWords * 64 : 1];
+  constexpr bool kPark = IsSeg<Acc>::value || std::is_same_v<Acc, IntAcc> || E > kScanE;
+  __shared__ uint32_t park_sh[kPark ? ScanWave<F, S, Acc, E>::kStashWords * 64 : 1];
   // The probes of the segment-start search do not depend on the tile: they
   // go out with the ticket.
   HeadProbe pr{0, 0};
@@ -974,10 +993,10 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   __syncthreads();
   const int64_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)tile_sh);
   lb.tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)tag_sh);
-  auto w = scan_wave_at<F, S, Acc>(tile, n);
+  auto w = scan_wave_at<F, S, Acc, E>(tile, n);
   w.template load<kEven>(x, seg);
   if constexpr (IsSeg<Acc>::value)
-    tile_heads(w, seg, pr, tile * blockDim.x * kScanE, (int64_t)blockDim.x * kScanE, heads_sh, wfirst_sh);
+    tile_heads(w, seg, pr, tile * blockDim.x * E, (int64_t)blockDim.x * E, heads_sh, wfirst_sh);
   w.fold(f);
   Acc total;
   const Acc before = block_wave_prefix(w.wave_total, lds, &total);

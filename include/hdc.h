@@ -312,8 +312,8 @@ typedef struct hdc_batch_call {
 
 /*
  * Many independent calls of one class -- same dtype, map callable f, fold
- * callable g and accumulation -- in one grouped launch plus one combine
- * launch per 32 calls: y = f(x) (when f and the call's y are non-NULL) and
+ * callable g and accumulation -- in one grouped launch per 32 calls, plus
+ * one combine launch where they make many chunks: y = f(x) (when f and the call's y are non-NULL) and
  * *out = the fold of g over x, each call exactly as hdc_map_reduce /
  * hdc_transform_reduce define it.  `calls` is a HOST array read during this
  * call (the table is passed to the kernels by value, so the launches can be

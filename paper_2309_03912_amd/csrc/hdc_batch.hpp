@@ -1,7 +1,7 @@
 // Grouped batch: many independent map + reduce calls of one class (same
-// storage type, callables and fold) in one grouped launch and one combine
-// launch.  The call table is a by-value kernel argument (no host-to-device
-// copy, so the pair of launches can be recorded into a graph as is).
+// storage type, callables and fold) in one grouped launch and, where
+// there are more chunks than compute units, one combine launch.  The call table is a by-value kernel argument (no host-to-device
+// copy, so the launches can be recorded into a graph as they are).
 //
 // Every call is cut into chunks of `chunk_vecs` 16-byte vectors; the global
 // chunk index space is the concatenation of all calls' chunks.  A block takes
@@ -38,9 +38,60 @@ struct BatchTable {
   BatchCall call[kBatchMax];
 };
 
-template <class FM, class F, class S, class Acc, int U>
+// Fold chunk partials [lo, hi) of one call, as read by get(k), and write the
+// call's result: the first kBatchFold threads stride over them in chunk order,
+// then the fixed block reduction (the waves beyond add zero states, so the bits
+// do not depend on the block).
+constexpr int kBatchFold = 256;
+
+template <class Acc>
+using BatchFoldT = std::conditional_t<std::is_same_v<Acc, CompAcc>, double, Acc>;
+
+template <class Acc, class Get>
+__device__ __forceinline__ void batch_fold(Get get, int64_t lo, int64_t hi, void* out, BatchFoldT<Acc>* lds) {
+  const bool mine = threadIdx.x < kBatchFold;
+  if constexpr (std::is_same_v<Acc, CompAcc>) {
+    double d = 0.0;
+    for (int64_t k = lo + threadIdx.x; mine && k < hi; k += kBatchFold) {
+      const CompAcc q = get(k);
+      d += __builtin_isfinite(q.s) ? (double)q.s + (double)q.c : (double)q.s;
+    }
+    d = block_reduce(d, AddF64{}, lds);
+    if (threadIdx.x == 0) *static_cast<double*>(out) = d;
+  } else {
+    Acc a = Acc::zero();
+    for (int64_t k = lo + threadIdx.x; mine && k < hi; k += kBatchFold) a = Acc::merge(a, get(k));
+    a = block_reduce(a, MergeOp<Acc>{}, lds);
+    if (threadIdx.x == 0) {
+      if constexpr (std::is_same_v<Acc, PlainAcc>)
+        *static_cast<float*>(out) = a.s;
+      else
+        *static_cast<int64_t*>(out) = (int64_t)a.s;
+    }
+  }
+}
+
+// The result of a call without elements.
+template <class Acc>
+__device__ __forceinline__ void write_empty(void* out) {
+  if constexpr (std::is_same_v<Acc, PlainAcc>)
+    *static_cast<float*>(out) = 0.0f;
+  else
+    *static_cast<uint64_t*>(out) = 0;  // a double or an int64
+}
+
+// kOne: the grid is one block per chunk, and `ticket` kTicketWords zero words
+// (left zero).  The chunks of a call are counted on the call's own counter and
+// the block that arrives last folds them: no second launch.  (kBatchMax
+// counters fit a ticket 128 bytes apart.)  A kernel of its own: as a run-time
+// branch it cost the two-launch form 9% (32 calls of up to 2^24 int32: 97.9 ->
+// 106.5 us).
+constexpr int kBatchStride = 32;
+static_assert((kBatchMax - 1) * kBatchStride < (int)kTicketWords);
+
+template <class FM, class F, class S, class Acc, int U, bool kOne>
   requires device_callable<F> && device_callable<FM>
-__global__ __launch_bounds__(1024) void batch_kernel(FM fm, F f, BatchTable t, Acc* partials) {
+__global__ __launch_bounds__(1024) void batch_kernel(FM fm, F f, BatchTable t, Acc* partials, uint32_t* ticket) {
   __shared__ Acc lds[kMaxWaves];
   const int64_t B = blockDim.x;
   const int64_t tid = threadIdx.x;
@@ -142,38 +193,35 @@ __global__ __launch_bounds__(1024) void batch_kernel(FM fm, F f, BatchTable t, A
 #pragma unroll
     for (int k = 1; k < KV; ++k) tt = Acc::merge(tt, acc[k]);
     tt = block_reduce(tt, MergeOp<Acc>{}, lds);
-    if (tid == 0) partials[c] = tt;
+    if constexpr (kOne) {
+      const int64_t lo = t.prefix[i], chunks = t.prefix[i + 1] - lo;
+      __shared__ int last;
+      __shared__ BatchFoldT<Acc> fold_lds[kMaxWaves];
+      if (tid == 0) {
+        last = 1;
+        if (chunks > 1) {
+          publish_partial(partials, c, tt);
+          last = arrive(ticket + i * kBatchStride, (uint32_t)chunks);
+        }
+      }
+      __syncthreads();
+      if (last)
+        batch_fold<Acc>([&](int64_t k) { return chunks > 1 ? read_partial(partials, k) : tt; }, lo, lo + chunks,
+                        call.out, fold_lds);
+      if (c == 0 && tid < t.count && t.prefix[tid + 1] == t.prefix[tid]) write_empty<Acc>(t.call[tid].out);
+      return;  // the block's only chunk
+    } else {
+      if (tid == 0) partials[c] = tt;
+    }
   }
 }
 
-// One block per call folds that call's chunk partials: thread-strided in
-// chunk order, then the fixed block reduction.
+// One block per call folds that call's chunk partials.
 template <class Acc>
-__global__ __launch_bounds__(256) void batch_combine_kernel(BatchTable t, const Acc* partials) {
+__global__ __launch_bounds__(kBatchFold) void batch_combine_kernel(BatchTable t, const Acc* partials) {
+  __shared__ BatchFoldT<Acc> lds[kMaxWaves];
   const int c = blockIdx.x;
-  const int64_t lo = t.prefix[c], hi = t.prefix[c + 1];
-  void* out = t.call[c].out;
-  if constexpr (std::is_same_v<Acc, CompAcc>) {
-    __shared__ double lds[kMaxWaves];
-    double d = 0.0;
-    for (int64_t k = lo + threadIdx.x; k < hi; k += blockDim.x) {
-      const CompAcc q = partials[k];
-      d += __builtin_isfinite(q.s) ? (double)q.s + (double)q.c : (double)q.s;
-    }
-    d = block_reduce(d, AddF64{}, lds);
-    if (threadIdx.x == 0) *static_cast<double*>(out) = d;
-  } else {
-    __shared__ Acc lds[kMaxWaves];
-    Acc a = Acc::zero();
-    for (int64_t k = lo + threadIdx.x; k < hi; k += blockDim.x) a = Acc::merge(a, partials[k]);
-    a = block_reduce(a, MergeOp<Acc>{}, lds);
-    if (threadIdx.x == 0) {
-      if constexpr (std::is_same_v<Acc, PlainAcc>)
-        *static_cast<float*>(out) = a.s;
-      else
-        *static_cast<int64_t*>(out) = (int64_t)a.s;
-    }
-  }
+  batch_fold<Acc>([&](int64_t k) { return partials[k]; }, t.prefix[c], t.prefix[c + 1], t.call[c].out, lds);
 }
 
 }  // namespace hdc

@@ -34,7 +34,7 @@ struct Tuning {
   int chunk = 4096;
   int small_seg = 128;
   int seg_per_wave = 8;
-  // reductions: 1 = one launch (the last block folds), 2 = two launches;
+  // reductions and batches: 1 = one launch (the last block folds), 2 = two launches;
   // segmented reduce: 1 = tiled schedule, 2 = planned schedule
   int passes = 2;
 };
@@ -241,7 +241,7 @@ hdc_status run_segmented(const hdc_functor& f, hdc_dtype dt, const void* x, cons
 // fit is refused (HDC_ERR_WORKSPACE) before anything is launched.
 hdc_status run_batch(const hdc_functor* fm, const hdc_functor& g, hdc_dtype dt, hdc_accum acc,
                      const hdc_batch_call* calls, const int32_t* idx, int cnt, void* ws, size_t ws_bytes,
-                     const Tuning& t, hipStream_t st);
+                     uint32_t* ticket, const Tuning& t, hipStream_t st);
 
 // `slot`: see launch_scan; NULL: the look-back nodes go to the workspace.
 hdc_status run_scan(const hdc_functor& f, hdc_dtype dt, const void* x, void* y, int64_t n, hdc_accum acc,

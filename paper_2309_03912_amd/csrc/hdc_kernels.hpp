@@ -405,23 +405,26 @@ __device__ __forceinline__ Acc read_partial(const Acc* slots, int64_t i) {
   return a;
 }
 
-// Count block b of G on the ticket: true for the block that arrives last.
-// Called by one thread, the one that made the block's agent-scope stores:
-// the wait for them is in its own wavefront's memory counter.
-__device__ __forceinline__ bool arrive_last(uint32_t* ticket, uint32_t b, uint32_t G) {
+// Count one of `members` arrivals on counter c: true for the last, which sets
+// it back to 0.  Called by one thread, the one that made the block's
+// agent-scope stores: the wait for them is in its own wavefront's memory counter.
+__device__ __forceinline__ bool arrive(uint32_t* c, uint32_t members) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores above are complete at agent scope
-  auto count = [](uint32_t* c, uint32_t members) {
-    if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return false;
-    __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
-  };
+  if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return false;
+  __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
+// Count block b of G on the ticket: true for the block that arrives last.
+// Called as `arrive` is.
+__device__ __forceinline__ bool arrive_last(uint32_t* ticket, uint32_t b, uint32_t G) {
   uint32_t groups = G;
   if (G > 2 * kTicketFan) {
     const uint32_t g = b % kTicketFan;
-    if (!count(ticket + (1 + g) * kTicketStride, (G - g + kTicketFan - 1) / kTicketFan)) return false;
+    if (!arrive(ticket + (1 + g) * kTicketStride, (G - g + kTicketFan - 1) / kTicketFan)) return false;
     groups = kTicketFan;
   }
-  return count(ticket, groups);
+  return arrive(ticket, groups);
 }
 
 // ---------------------------------------------------------------------------

@@ -254,9 +254,11 @@ hdc_status hdc_map_reduce(const hdc_functor* f, const hdc_functor* g,
  *  - any value but 1 (the default): one pass.  Tiles are handed out in
  *    launch order.  Each tile publishes its total as a leaf of a radix-64
  *    tree (the last tile of a group also the group's node), and folds its
- *    carry from at most 63 nodes per tree level, in a fixed order.  The carry between tiles is
- *    fp64 for floats and int64 for integers.  x is read once.  A small
- *    clear kernel runs first on the same stream.  Every wait is bounded:
+ *    carry from at most 63 nodes per tree level, in a fixed order.  The
+ *    carry between tiles is fp64 for floats and int64 for integers.  x is
+ *    read once.  The nodes of up to 256 tiles lie in library memory; for
+ *    more, a small clear kernel runs first on the same stream.  Every wait
+ *    is bounded:
  *    if one gives up, the call's output is invalid and hdc_scan_status
  *    reports it.  Tiles start in order, so a give-up is not expected.
  *  - 1: three passes (tile sums, tile offsets, tile scans) with no waiting

@@ -350,17 +350,23 @@ static __device__ __align__(256) uint32_t tickets[(size_t)kTicketSlots * kTicket
 constexpr int kScanSlots = 1 << 10;
 static __device__ __align__(256) uint64_t scan_slots[(size_t)kScanSlots * kScanSlotWords];
 
+// The slots of single passes of more tiles, up to kScanLongTiles, for the first
+// kScanLongSlots keys that run one (13 MB).
+constexpr int kScanLongSlots = 1 << 5;
+static __device__ __align__(256) uint64_t scan_long_slots[(size_t)kScanLongSlots * kScanLongWords];
+
 struct TicketTable {
   uint32_t* base = nullptr;  // device addresses of `tickets` and `scan_slots` on this device
   uint64_t* scan_base = nullptr;
-  std::map<std::pair<const void*, hipStream_t>, int> slot;
+  uint64_t* long_base = nullptr;  // of `scan_long_slots`
+  std::map<std::pair<const void*, hipStream_t>, int> slot, long_slot;
 };
 std::mutex g_ticket_mu;
 TicketTable g_ticket_tables[kMaxDevices];
 
 // The slot number of workspace buffer `ws` and stream `st` on the current
 // device, or -1 when none is left, and the device's table.
-hdc_status slot_for(const void* ws, hipStream_t st, int* slot, const TicketTable** table) {
+hdc_status slot_for(const void* ws, hipStream_t st, int* slot, TicketTable** table) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail(HDC_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
@@ -368,11 +374,13 @@ hdc_status slot_for(const void* ws, hipStream_t st, int* slot, const TicketTable
   std::lock_guard<std::mutex> g(g_ticket_mu);
   TicketTable& tt = g_ticket_tables[dev];
   if (!tt.base) {
-    void *p = nullptr, *q = nullptr;
+    void *p = nullptr, *q = nullptr, *l = nullptr;
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(tickets));
     if (e == hipSuccess) e = hipGetSymbolAddress(&q, HIP_SYMBOL(scan_slots));
-    if (e != hipSuccess || !p || !q) return fail(HDC_ERR_HIP, "hipGetSymbolAddress(tickets): %s", hipGetErrorString(e));
+    if (e == hipSuccess) e = hipGetSymbolAddress(&l, HIP_SYMBOL(scan_long_slots));
+    if (e != hipSuccess || !p || !q || !l) return fail(HDC_ERR_HIP, "hipGetSymbolAddress(tickets): %s", hipGetErrorString(e));
     tt.scan_base = static_cast<uint64_t*>(q);
+    tt.long_base = static_cast<uint64_t*>(l);
     tt.base = static_cast<uint32_t*>(p);
   }
   *table = &tt;
@@ -392,25 +400,33 @@ hdc_status slot_for(const void* ws, hipStream_t st, int* slot, const TicketTable
 // The ticket of workspace buffer `ws` and stream `st`, or NULL.
 hdc_status ticket_for(const void* ws, hipStream_t st, uint32_t** out) {
   int slot = -1;
-  const TicketTable* tt = nullptr;
+  TicketTable* tt = nullptr;
   HDC_TRY(slot_for(ws, st, &slot, &tt));
   *out = slot < 0 ? nullptr : tt->base + (size_t)slot * kTicketWords;
   return HDC_OK;
 }
 
-// The look-back slot of workspace buffer `ws` and stream `st`, or NULL.
-hdc_status scan_slot_for(const void* ws, hipStream_t st, uint64_t** out) {
-  int slot = -1;
-  const TicketTable* tt = nullptr;
-  HDC_TRY(slot_for(ws, st, &slot, &tt));
-  *out = slot < 0 || slot >= kScanSlots ? nullptr : tt->scan_base + (size_t)slot * kScanSlotWords;
-  return HDC_OK;
-}
-
-// A single pass of 2 .. kScanSlotTiles tiles keeps its look-back nodes in a slot.
-bool scan_takes_slot(int64_t n, const Tuning& t) {
+// The look-back slot of a scan of n elements with workspace buffer `ws` on
+// stream `st`; NULL where it needs none or none is left.
+hdc_status scan_slot_for(int64_t n, const Tuning& t, const void* ws, hipStream_t st, uint64_t** out) {
+  *out = nullptr;
   const int64_t tile = (int64_t)t.block * kScanE, tiles = (n + tile - 1) / tile;
-  return t.unroll != 1 && tiles > 1 && tiles <= kScanSlotTiles;
+  if (t.unroll == 1 || tiles <= 1 || tiles > kScanLongTiles) return HDC_OK;
+  int slot = -1;
+  TicketTable* tt = nullptr;
+  HDC_TRY(slot_for(ws, st, &slot, &tt));
+  if (tiles <= kScanSlotTiles) {
+    if (slot >= 0 && slot < kScanSlots) *out = tt->scan_base + (size_t)slot * kScanSlotWords;
+    return HDC_OK;
+  }
+  std::lock_guard<std::mutex> g(g_ticket_mu);
+  auto it = tt->long_slot.find({ws, st});
+  if (it == tt->long_slot.end()) {
+    if (tt->long_slot.size() >= (size_t)kScanLongSlots) return HDC_OK;
+    it = tt->long_slot.emplace(std::make_pair(ws, st), (int)tt->long_slot.size()).first;
+  }
+  *out = tt->long_base + (size_t)it->second * kScanLongWords;
+  return HDC_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -731,7 +747,7 @@ hdc_status hdc_scan(const hdc_functor* f, hdc_dtype dt, const void* x, void* y, 
   log_dispatch(exclusive ? "scan (exclusive)" : "scan (inclusive)", dt, acc, n, t,
                t.unroll == 1 ? "three passes" : "one pass (tree carry)", workspace ? "caller" : "library");
   uint64_t* slot = nullptr;
-  if (scan_takes_slot(n, t)) HDC_TRY(scan_slot_for(ws, st, &slot));
+  HDC_TRY(scan_slot_for(n, t, ws, st, &slot));
   return run_scan(*f, dt, x, y, n, acc, exclusive, ws, slot, t, st);
 }
 
@@ -761,7 +777,7 @@ hdc_status hdc_segmented_scan(const hdc_functor* f, hdc_dtype dt, const void* x,
   log_dispatch(exclusive ? "segmented_scan (exclusive)" : "segmented_scan (inclusive)", dt, acc, total, t,
                t.unroll == 1 ? "three passes" : "one pass (tree carry)", workspace ? "caller" : "library");
   uint64_t* slot = nullptr;
-  if (scan_takes_slot(total, t)) HDC_TRY(scan_slot_for(ws, st, &slot));
+  HDC_TRY(scan_slot_for(total, t, ws, st, &slot));
   return run_segmented_scan(*f, dt, x, offsets, num_segments, y, total, acc, exclusive, ws, slot, t, st);
 }
 

@@ -704,12 +704,13 @@ struct ScanCarry<SegAcc<Acc>> {
 // when its tag is the launch's.  Two places for them:
 //  * the workspace, whose words scan_lb_clear_kernel sets to zero first, on
 //    the same stream; the tag is 1;
-//  * for up to kScanSlotTiles tiles a slot of library-owned memory (one per
-//    workspace and stream, zero when the library is loaded), with no clear
-//    launch: the slot's ticket carries a launch epoch in its upper half, which
-//    the block that draws the last tile moves on, and the tag is the epoch +
-//    1.  Only these kernels write a slot, so a word of an earlier launch has
-//    an earlier tag (until it would repeat, after 2^32 launches).
+//  * for up to kScanLongTiles tiles a slot of library-owned memory (one per
+//    workspace and stream, zero when the library is loaded; a small one holds
+//    kScanSlotTiles tiles), with no clear launch: the slot's ticket carries a
+//    launch epoch in its upper half, which the block that draws the last tile
+//    moves on, and the tag is the epoch + 1.  Only these kernels write a slot,
+//    so a word of an earlier launch has an earlier tag (until it would repeat,
+//    after 2^32 launches).
 struct ScanLB {
   uint32_t* ticket;   // next tile to hand out (workspace)
   uint64_t* ticket64; // epoch and next tile (slot), or NULL
@@ -720,6 +721,7 @@ struct ScanLB {
 
 constexpr int64_t kScanSlotTiles = 256;
 constexpr int64_t kScanSlotWords = 16 + 3 * (kScanSlotTiles + kScanSlotTiles / 64);  // the ticket's line, the nodes
+constexpr int64_t kScanLongTiles = 1 << 14;
 
 // What a slot launch that gave up leaves in the status word (its own mark, so
 // that the first tile can clear an earlier call's word at any time).
@@ -777,6 +779,7 @@ __host__ __device__ constexpr int64_t tree_nodes(int64_t tiles) {
   }
   return sum;
 }
+constexpr int64_t kScanLongWords = 16 + 3 * tree_nodes(kScanLongTiles);  // 400 KB
 
 // Ordered fold of the values of lanes 0 .. m-1 (m >= 1, uniform), in lane
 // order, returned in every lane.  Lane l's value is in words

@@ -256,8 +256,9 @@ hdc_status hdc_map_reduce(const hdc_functor* f, const hdc_functor* g,
  *    tree (the last tile of a group also the group's node), and folds its
  *    carry from at most 63 nodes per tree level, in a fixed order.  The
  *    carry between tiles is fp64 for floats and int64 for integers.  x is
- *    read once.  The nodes of up to 256 tiles lie in library memory; for
- *    more, a small clear kernel runs first on the same stream.  Every wait
+ *    read once.  The nodes of up to 16384 tiles lie in library memory (for
+ *    the first workspaces and streams that scan); else a small clear kernel
+ *    runs first on the same stream.  Every wait
  *    is bounded:
  *    if one gives up, the call's output is invalid and hdc_scan_status
  *    reports it.  Tiles start in order, so a give-up is not expected.

@@ -147,8 +147,10 @@ inline hdc_status launch_exact_f16_dot(const void* x, const void* z, int64_t n, 
 
 // Tiled schedule of the segmented reduce (t.passes == 1): the tile pass and
 // the fold of segments that span tiles, in the same launch when the block
-// that arrives last can hold all tiles, else in a second one.  The workspace
-// is counted in two halves of 32 bytes per tile.
+// that arrives last can hold all tiles and the segments are not far more than
+// the elements (their zeros take the wavefronts of the second launch, which
+// are by the segments), else in a second one.  The workspace is counted in
+// two halves of 32 bytes per tile.
 //
 // `total` bounds the elements (it comes with the workspace).  Few elements are
 // cut into smaller tiles than the tuning's, down to kMinChunk elements, while
@@ -183,7 +185,7 @@ hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64
   tl.tile_vecs = tile / S::kVec;
   int64_t tiles = total / tile + 2;  // at most: the head joins the first tile, the tail the last
   if (tiles > tl.cap) tiles = tl.cap;
-  if (tiles > seg_last_tiles(block)) ticket = nullptr;
+  if (tiles > seg_last_tiles(block) || nseg > kMinChunk * tiles) ticket = nullptr;
   // one launch: a range of more elements than the workspace is sized for must not exceed the block's tiles
   if (ticket && tl.cap > seg_last_tiles(block)) tl.cap = seg_last_tiles(block);
   tl.one = ticket != nullptr;

@@ -432,8 +432,10 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int64_t* __restr
 // when the tile started; `last`: it started in the tile and runs past its
 // end), and the parts of a segment that spans tiles are folded in tile order:
 // for few tiles by the block that arrives last in the same launch, else by a
-// second small launch (which also writes 0 for empty segments; in one launch
-// the tile that reaches their position does).  No plan is built, and the work of every wavefront is the same number of vectors.
+// second small launch.  The tiles pass over empty segments; their 0 comes from
+// the second launch or, in one launch, from all wavefronts before their tiles
+// (zero_empty).  No plan is built, and the work of every wavefront is the same
+// number of vectors.
 // The unaligned head of the range belongs to the first tile, its tail to the
 // last one.  Everything is a fold of fixed values in a fixed order, so the
 // results are reproducible bit for bit.
@@ -665,16 +667,32 @@ struct TileWave {
     if (j - bbase >= 32) load_batch(j);
   }
 
-  // The segment holding tile position 0 (the last j with off[j] - off[0] <=
-  // base), from a finder started for `base`: its remaining rounds run here.
-  __device__ void locate(SegFinder& fd) {
+  // The segment holding position `pos` (the last j with off[j] - off[0] <=
+  // pos) and its batch, from a finder started for it: the remaining rounds run
+  // here.
+  __device__ void place(SegFinder& fd, int64_t pos) {
     while (!fd.final_round()) fd.next(off, S_, lane);
     bbase = fd.a;
     set_batch(fd.probe == INT64_MAX ? INT64_MAX : fd.probe - lo);
-    const int cnt = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < fd.n && bnd <= base));
-    j = fd.a + cnt - 1;
+    j = fd.a + __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < fd.n && bnd <= pos)) - 1;
+  }
+  // The segment holding tile position 0, from a finder started for `base`.
+  __device__ void locate(SegFinder& fd) {
+    place(fd, base);
     started = read_lane(bnd, j - bbase) >= base;
     nb = bound(j + 1);
+  }
+  // The batch's last offset is not past `pos`: search on from there for the
+  // segment holding it.  A run of empty segments costs one search (six
+  // dependent reads at most) however long it is: step by step, 100,000 of them
+  // cost 800 us.
+  __device__ void search_on(int64_t pos) {
+    SegFinder fd;
+    fd.aim(lo + pos);
+    fd.a = bbase + 63;
+    fd.n = S_ + 1 - fd.a;
+    fd.issue(off, S_, lane);
+    place(fd, pos);
   }
 
   __device__ void put(uint64_t* p, uint64_t v) const {
@@ -693,26 +711,20 @@ struct TileWave {
     }
     if (kDense && !started) ended = (uint32_t)j + 1;
   }
-  // Leave segment j at its end nb: the next non-empty segment starts there
-  // (the empty ones before it get 0).
+  // Leave segment j at its end nb: the next non-empty segment starts there.
   __device__ void advance() {
     const int32_t b = nb;
-    for (;;) {
-      ++j;
+    ++j;
+    nb = bound(j + 1);
+    if (nb == b) {  // empty ones in between
+      const int64_t pos = base + b;
+      if (read_lane(bnd, 63) > pos)
+        j = bbase + __builtin_popcountll(__builtin_amdgcn_ballot_w64(bnd <= pos)) - 1;
+      else
+        search_on(pos);
       nb = bound(j + 1);
-      if (nb != b) break;
-      if (kDense && lane == 0) store_result<Acc>(out, j, Acc::zero());
     }
     started = true;
-  }
-  // 0 to the empty segments from index i on that end at position `pos` (relative to off[0]).
-  __device__ void zero_empty(int32_t i, int64_t pos) {
-    for (;; i += 64) {
-      const int32_t k = i + lane;
-      const bool empty = k < S_ && off[(int64_t)k + 1] - lo == pos;
-      if (empty) store_result<Acc>(out, k, Acc::zero());
-      if (~__builtin_amdgcn_ballot_w64(empty) != 0) break;
-    }
   }
 
   // Split N terms at the segment ends below pe: term k sits at tile position
@@ -756,6 +768,19 @@ struct TileWave {
     }
   }
 
+  // The next batch for a chunk that the present one ends inside of; a run of
+  // empty segments longer than a batch is passed over.
+  __device__ void next_batch() {
+    const int64_t pos = read_lane(bnd, 63);
+    if (read_lane(bnd, 0) == pos) {
+      const int32_t keep = j;
+      search_on(pos);
+      j = keep;
+    } else {
+      load_batch(bbase + 63);
+    }
+  }
+
   // A chunk with many segment ends, by one segmented scan.  The batch's lanes
   // mark the segment starts of the chunk in a bitmap; every lane folds its KV
   // terms, starting over at each mark, and leaves the running fold of every
@@ -776,7 +801,7 @@ struct TileWave {
       if (bbase + lane > j && o < ce - cs) atomicOr(&lds->bits[(uint32_t)o >> 5], 1u << ((uint32_t)o & 31));
       __builtin_amdgcn_wave_barrier();
       if (!more()) break;
-      load_batch(bbase + 63);
+      next_batch();
     }
     __builtin_amdgcn_wave_barrier();
     const uint32_t at = (uint32_t)lane * KV;
@@ -829,16 +854,14 @@ struct TileWave {
       int64_t e = dpp_words<0x130, 0xF>(bnd) - base - cs;
       e = lane == 63 ? INT64_MAX : e;  // wave_shl:1 gives the next offset; lane 63 has none
       const int32_t i = bbase + lane;
-      if (i >= j && e < ce - cs) {  // segment i ends inside the chunk
-        Acc v = Acc::zero();
-        if (e > s) {
-          const int32_t p = (int32_t)e - 1;
-          if (p < 0) {
-            v = open;
-          } else {
-            v = lds->vals[p];
-            if (s < (p & ~(KV - 1))) v = Acc::merge(lds->pre[p / KV], v);
-          }
+      if (i >= j && e < ce - cs && e > s) {  // segment i ends inside the chunk and is not empty
+        const int32_t p = (int32_t)e - 1;
+        Acc v;
+        if (p < 0) {
+          v = open;
+        } else {
+          v = lds->vals[p];
+          if (s < (p & ~(KV - 1))) v = Acc::merge(lds->pre[p / KV], v);
         }
         if (i == j && !started)
           put(&st.first[tile], acc_word(v));
@@ -847,7 +870,7 @@ struct TileWave {
       }
       __builtin_amdgcn_wave_barrier();
       if (!more()) break;
-      load_batch(bbase + 63);
+      next_batch();
     }
     __builtin_amdgcn_wave_barrier();
     if (!started) ended = (uint32_t)j + 1;
@@ -938,8 +961,6 @@ struct TileWave {
     acc = Acc::zero();
     lane0 = true;
     ended = 0;
-    if (kDense && first_tile)  // the segments before the first non-empty one
-      for (int32_t i = lane; i < j; i += 64) store_result<Acc>(out, i, Acc::zero());
 
     if (first_tile && g.head > 0) scalar_step(0, (int32_t)g.head);
     // Fold the step at vector v0 from buffer d.
@@ -1013,7 +1034,6 @@ struct TileWave {
     uint64_t meta = 0;
     if (nb == len) {
       finish(total);
-      if constexpr (kDense) zero_empty(j + 1, base + len);
     } else if (started) {
       if (lane == 0) put(&st.last[tile], acc_word(total));
       meta = kTileLast;
@@ -1105,6 +1125,30 @@ __device__ __forceinline__ void seg_fold_last(const SegTiles& st, int32_t ntiles
   }
 }
 
+// 0 to every empty segment, by all W wavefronts of the grid, w being this one.
+// The launcher keeps S below kMinChunk times the tiles, so a lane takes a few
+// rounds of kRound segments, their offsets all loaded at once.
+template <class Acc>
+__device__ __forceinline__ void zero_empty(const int64_t* __restrict__ off, int64_t S_, int64_t w, int64_t W,
+                                           int lane, void* out) {
+  constexpr int kRound = 4;
+  for (int64_t b = w * 64; b < S_; b += kRound * W * 64) {
+    int64_t s[kRound], e[kRound];
+#pragma unroll
+    for (int u = 0; u < kRound; ++u) {
+      if (b + u * W * 64 >= S_) break;  // uniform
+      const int64_t i = b + u * W * 64 + lane, k = i < S_ ? i : S_ - 1;
+      s[u] = off[k];
+      e[u] = off[k + 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kRound; ++u) {
+      const int64_t i = b + u * W * 64 + lane;
+      if (i < S_ && e[u] <= s[u]) store_result<Acc>(out, i, Acc::zero());
+    }
+  }
+}
+
 // What bounds it: HBM where segment ends are rare, the vector ALU where there
 // are many (kDenseEnds).  `ticket`: the one-launch form (at most
 // seg_last_tiles(blockDim.x) tiles, which the launcher knows from the
@@ -1123,10 +1167,12 @@ __global__ __launch_bounds__(kTilesMaxBlock) void seg_tiles_kernel(F f, const el
   // the tile geometry (it needs no position yet).
   SegFinder fd{};
   fd.begin(off, (int32_t)S_, lane);
+  if (kDense && st.one) zero_empty<Acc>(off, S_, w, W, lane, out);
   const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
+  if (g.ntiles == 0) return;
   // More tiles than the workspace holds: every segment is folded whole by
-  // one wavefront.  (No element at all: every segment is empty.)
-  if (g.ntiles > st.cap || g.ntiles == 0) {
+  // one wavefront.
+  if (g.ntiles > st.cap) {
     for (int64_t j = w; j < S_; j += W) {
       const Acc r = wave_fold_range<F, S, Acc, U>(f, x, off[j], off[j + 1], lane);
       if (lane == 0) store_result<Acc>(out, j, r);
@@ -1161,7 +1207,7 @@ __global__ __launch_bounds__(256) void seg_tiles_combine_kernel(const elem_t<S>*
                                                                 const int64_t* __restrict__ off, int64_t S_,
                                                                 SegTiles st, void* out) {
   const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
-  if (g.ntiles > st.cap || g.ntiles == 0) return;  // the tile pass folded every segment whole
+  if (g.ntiles > st.cap) return;  // the tile pass folded every segment whole
   constexpr bool kComp = std::is_same_v<Acc, CompAcc>;
   // part k of a segment whose first tile is ts
   auto part = [&](int64_t ts, int64_t k) {
@@ -1176,7 +1222,7 @@ __global__ __launch_bounds__(256) void seg_tiles_combine_kernel(const elem_t<S>*
     if (j < S_) {
       const int64_t s = off[j] - g.lo, e = off[j + 1] - g.lo;
       if (e <= s) {
-        store_result<Acc>(out, j, Acc::zero());  // empty (the pass without the scan leaves it)
+        store_result<Acc>(out, j, Acc::zero());  // the tile pass leaves empty ones
       } else {
         ts = tile_of<S>(g, st.tile_vecs, s);
         te = tile_of<S>(g, st.tile_vecs, e - 1);

@@ -559,7 +559,7 @@ struct SegFinder {
   int64_t probe;    // this lane's probe of the round in flight; INT64_MAX if none
 
   __device__ void issue(const int64_t* off, int32_t S, int lane) {
-    step = n > 64 ? (n + 63) / 64 : 1;
+    step = n > 64 ? (n - 1) / 64 + 1 : 1;  // n + 63 may not fit 32 bits
     const int64_t idx = (int64_t)a + (int64_t)lane * step;
     const bool ok = step == 1 ? idx <= S : idx < (int64_t)a + n;
     probe = ok ? off[idx] : INT64_MAX;
@@ -759,7 +759,7 @@ struct TileWave {
       return;
     }
     if (j - bbase >= 48) load_batch(j);
-    const int ends = __builtin_popcountll(__builtin_amdgcn_ballot_w64(bbase + lane > j && bnd - base < ce));
+    const int ends = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane > j - bbase && bnd - base < ce));
     if (ends < kDenseEnds) {
       split<KV>(t, lane * KV, [](int k) { return k; }, cs, ce);
       lane0 = false;
@@ -798,7 +798,7 @@ struct TileWave {
     auto more = [&]() { return read_lane(bnd, 63) - base < ce; };  // the batch ends inside the chunk
     for (;;) {
       const int64_t o = bnd - base - cs;
-      if (bbase + lane > j && o < ce - cs) atomicOr(&lds->bits[(uint32_t)o >> 5], 1u << ((uint32_t)o & 31));
+      if (lane > j - bbase && o < ce - cs) atomicOr(&lds->bits[(uint32_t)o >> 5], 1u << ((uint32_t)o & 31));
       __builtin_amdgcn_wave_barrier();
       if (!more()) break;
       next_batch();
@@ -853,7 +853,7 @@ struct TileWave {
       const int64_t s = bnd - base - cs;
       int64_t e = dpp_words<0x130, 0xF>(bnd) - base - cs;
       e = lane == 63 ? INT64_MAX : e;  // wave_shl:1 gives the next offset; lane 63 has none
-      const int32_t i = bbase + lane;
+      const int64_t i = (int64_t)bbase + lane;
       if (i >= j && e < ce - cs && e > s) {  // segment i ends inside the chunk and is not empty
         const int32_t p = (int32_t)e - 1;
         Acc v;

@@ -146,9 +146,9 @@ inline hdc_status launch_exact_f16_dot(const void* x, const void* z, int64_t n, 
 }
 
 // Tiled schedule of the segmented reduce (t.passes == 1): the tile pass and
-// the fold of segments that span tiles, in the same launch when the block
-// that arrives last can hold all tiles and the segments are not far more than
-// the elements (their zeros take the wavefronts of the second launch, which
+// the fold of segments that span tiles, by one block (in the same launch, if a
+// ticket is left) when it can hold all tiles and the segments are not far more
+// than the elements (their zeros take the wavefronts of the second launch, which
 // are by the segments), else in a second one.  The workspace is counted in
 // two halves of 32 bytes per tile.
 //
@@ -185,16 +185,17 @@ hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64
   tl.tile_vecs = tile / S::kVec;
   int64_t tiles = total / tile + 2;  // at most: the head joins the first tile, the tail the last
   if (tiles > tl.cap) tiles = tl.cap;
-  if (tiles > seg_last_tiles(block) || nseg > kMinChunk * tiles) ticket = nullptr;
-  // one launch: a range of more elements than the workspace is sized for must not exceed the block's tiles
-  if (ticket && tl.cap > seg_last_tiles(block)) tl.cap = seg_last_tiles(block);
-  tl.one = ticket != nullptr;
+  // by the sizes alone, not by whether a ticket is left: the passes and folds that follow give other bits
+  tl.one = tiles <= seg_last_tiles(block) && nseg <= kMinChunk * tiles;
+  if (!tl.one) ticket = nullptr;
+  // a range of more elements than the workspace is sized for must not exceed the block's tiles
+  if (tl.one && tl.cap > seg_last_tiles(block)) tl.cap = seg_last_tiles(block);
   const int64_t wpb = block / 64;
   int64_t g = (int64_t)cus * t.grid_mult;
   const int64_t need = (tiles + wpb - 1) / wpb;  // never more wavefronts than tiles
   if (g > need) g = need;
   if (g < 1) g = 1;
-  const bool dense = ticket || nseg * kDenseVecs * S::kVec > total;
+  const bool dense = tl.one || nseg * kDenseVecs * S::kVec > total;
   auto go = [&](auto U) {
     constexpr int kU = decltype(U)::value;
     if (dense)
@@ -213,6 +214,10 @@ hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64
   }
   HDC_TRY(check_launch("segmented tile launch"));
   if (ticket) return HDC_OK;
+  if (tl.one) {
+    seg_last_kernel<S, Acc><<<dim3(1), dim3(block), 0, st>>>((const T*)x, off, nseg, tl, out);
+    return check_launch("segmented last-fold launch");
+  }
   int64_t gc = (nseg + 255) / 256;  // one wavefront per 64 segments
   if (gc > (int64_t)cus * 8) gc = (int64_t)cus * 8;
   seg_tiles_combine_kernel<S, Acc><<<dim3((unsigned)gc), dim3(256), 0, st>>>((const T*)x, off, nseg, tl, out);

@@ -431,9 +431,10 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int64_t* __restr
 // its part of that segment to one of two slots (`first`: the segment was open
 // when the tile started; `last`: it started in the tile and runs past its
 // end), and the parts of a segment that spans tiles are folded in tile order:
-// for few tiles by the block that arrives last in the same launch, else by a
+// for few tiles by one block, the one that arrives last in the same launch
+// (or, with no ticket left, the only one of a second launch), else by a
 // second small launch.  The tiles pass over empty segments; their 0 comes from
-// the second launch or, in one launch, from all wavefronts before their tiles
+// that second launch or, for few tiles, from all wavefronts before their tiles
 // (zero_empty).  No plan is built, and the work of every wavefront is the same
 // number of vectors.
 // The unaligned head of the range belongs to the first tile, its tail to the
@@ -441,7 +442,7 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int64_t* __restr
 // results are reproducible bit for bit.
 // ===========================================================================
 
-// What a tile did (one launch only): the segment open at the tile's start
+// What a tile did (with SegTiles::one): the segment open at the tile's start
 // (started earlier) ended in it -- its index + 1 in the low half, else 0 -- or
 // ran through it (kTileThrough); and whether the tile wrote `last`.
 constexpr uint64_t kTileThrough = uint64_t(1) << 32;
@@ -450,14 +451,14 @@ constexpr uint64_t kTileLast = uint64_t(1) << 33;
 struct SegTiles {
   uint64_t* first;    // per tile: its part of the segment open at its start (a fold state's words)
   uint64_t* last;     // per tile: its part of a segment starting in it and running past its end
-  uint64_t* meta;     // per tile, in one launch: what it did
+  uint64_t* meta;     // per tile, with `one`: what it did
   int64_t cap;        // tiles the workspace holds
   int64_t tile_vecs;  // 16-byte vectors per tile
-  int32_t one;        // one launch: the block that arrives last folds the slots
+  int32_t one;        // few tiles: one block folds the slots
 };
 
-// In one launch the slots are stored write-through at agent scope: the block
-// that folds them may run on another XCD.  (For a second launch ordinary
+// With `one` the slots are stored write-through at agent scope: the block that
+// folds them in the same launch may run on another XCD.  (For a second launch ordinary
 // stores do, and 16,000 tiles' write-through ones took 2.6 us of 106.)
 __device__ __forceinline__ void put_word(uint64_t* p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1150,7 +1151,7 @@ __device__ __forceinline__ void zero_empty(const int64_t* __restrict__ off, int6
 }
 
 // What bounds it: HBM where segment ends are rare, the vector ALU where there
-// are many (kDenseEnds).  `ticket`: the one-launch form (at most
+// are many (kDenseEnds).  `ticket` (only with st.one: at most
 // seg_last_tiles(blockDim.x) tiles, which the launcher knows from the
 // workspace): the block that arrives last folds the segments that span tiles.
 template <class F, class S, class Acc, int U, bool kDense>
@@ -1196,7 +1197,18 @@ __global__ __launch_bounds__(kTilesMaxBlock) void seg_tiles_kernel(F f, const el
   if (last) seg_fold_last<Acc>(st, (int32_t)g.ntiles, out);
 }
 
-// Segments that span tiles (the two-launch form): their parts folded in tile
+// The second launch of few tiles without a ticket: the same fold by the same
+// number of threads as in one launch, so that the bits do not depend on how
+// many tickets are left.
+template <class S, class Acc>
+__global__ __launch_bounds__(kTilesMaxBlock) void seg_last_kernel(const elem_t<S>* __restrict__ x,
+                                                                  const int64_t* __restrict__ off, int64_t S_,
+                                                                  SegTiles st, void* out) {
+  const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
+  if (g.ntiles > 0 && g.ntiles <= st.cap) seg_fold_last<Acc>(st, (int32_t)g.ntiles, out);
+}
+
+// Segments that span tiles (the second launch of many tiles): their parts folded in tile
 // order (the part of the tile where the segment starts, then every later
 // tile's `first` part).  Each lane takes one segment; a segment spanning more
 // than kLaneTiles tiles is folded by the whole wavefront (wave_fold_items).

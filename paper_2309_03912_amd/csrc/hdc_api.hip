@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <unordered_map>
 #include <mutex>
 #include <string>
 #include <utility>
@@ -333,7 +334,7 @@ hdc_status scratch_address(void** out) {
 // Tickets of the one-launch reductions
 // ---------------------------------------------------------------------------
 
-// A one-launch reduction counts its finished blocks on a ticket (kTicketWords
+// A one-launch reduction counts its finished blocks on a ticket (kTicketCounters
 // counters) that must be 0 when the kernel starts; the kernel leaves it 0.
 // The tickets are library-owned device memory (an object of static storage,
 // so zero-initialized when the code object is loaded), one per workspace
@@ -341,9 +342,15 @@ hdc_status scratch_address(void** out) {
 // ticket at the same time, and calls that wrongly share a workspace across
 // streams can spoil each other's partials but not a ticket, which later calls
 // rely on.  Once every slot of a device is taken, calls with a new workspace
-// or stream use the two-launch form.
-constexpr int kTicketSlots = 1 << 11;  // 4352 bytes each
-static __device__ __align__(256) uint32_t tickets[(size_t)kTicketSlots * kTicketWords];
+// or stream use the two-launch form.  There are 65,536 of them, in 8 MiB:
+// kTicketGroups groups of kTicketStride tickets, whose counters interleave (a
+// counter of every ticket of the group in one 256-byte line).  The first
+// kTicketGroups tickets are handed out one per group, so that only later ones
+// share a line.
+constexpr int kTicketSlots = 1 << 16;
+constexpr int kTicketGroups = kTicketSlots / kTicketStride;
+constexpr size_t kTicketGroupWords = (size_t)kTicketCounters * kTicketStride;
+static __device__ __align__(256) uint32_t tickets[kTicketGroups * kTicketGroupWords];
 
 // Look-back slots of the single-pass scans of few tiles, for the first
 // kScanSlots of those keys (8 MiB); zero-initialized as the tickets are.
@@ -355,11 +362,18 @@ static __device__ __align__(256) uint64_t scan_slots[(size_t)kScanSlots * kScanS
 constexpr int kScanLongSlots = 1 << 5;
 static __device__ __align__(256) uint64_t scan_long_slots[(size_t)kScanLongSlots * kScanLongWords];
 
+using SlotKey = std::pair<const void*, hipStream_t>;
+struct SlotHash {
+  size_t operator()(const SlotKey& k) const {
+    return ((uintptr_t)k.first / 256 + 31 * (uintptr_t)k.second) * 0x9E3779B97F4A7C15u >> 16;
+  }
+};
+
 struct TicketTable {
   uint32_t* base = nullptr;  // device addresses of `tickets` and `scan_slots` on this device
   uint64_t* scan_base = nullptr;
   uint64_t* long_base = nullptr;  // of `scan_long_slots`
-  std::map<std::pair<const void*, hipStream_t>, int> slot, long_slot;
+  std::unordered_map<SlotKey, int, SlotHash> slot, long_slot;
 };
 std::mutex g_ticket_mu;
 TicketTable g_ticket_tables[kMaxDevices];
@@ -384,7 +398,7 @@ hdc_status slot_for(const void* ws, hipStream_t st, int* slot, TicketTable** tab
     tt.base = static_cast<uint32_t*>(p);
   }
   *table = &tt;
-  const std::pair<const void*, hipStream_t> key{ws, st};
+  const SlotKey key{ws, st};
   auto it = tt.slot.find(key);
   if (it == tt.slot.end()) {
     if (tt.slot.size() >= (size_t)kTicketSlots) {
@@ -402,7 +416,7 @@ hdc_status ticket_for(const void* ws, hipStream_t st, uint32_t** out) {
   int slot = -1;
   TicketTable* tt = nullptr;
   HDC_TRY(slot_for(ws, st, &slot, &tt));
-  *out = slot < 0 ? nullptr : tt->base + (size_t)slot * kTicketWords;
+  *out = slot < 0 ? nullptr : tt->base + slot % kTicketGroups * kTicketGroupWords + slot / kTicketGroups;
   return HDC_OK;
 }
 

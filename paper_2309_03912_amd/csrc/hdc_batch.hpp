@@ -80,14 +80,12 @@ __device__ __forceinline__ void write_empty(void* out) {
     *static_cast<uint64_t*>(out) = 0;  // a double or an int64
 }
 
-// kOne: the grid is one block per chunk, and `ticket` kTicketWords zero words
-// (left zero).  The chunks of a call are counted on the call's own counter and
-// the block that arrives last folds them: no second launch.  (kBatchMax
-// counters fit a ticket 128 bytes apart.)  A kernel of its own: as a run-time
-// branch it cost the two-launch form 9% (32 calls of up to 2^24 int32: 97.9 ->
-// 106.5 us).
-constexpr int kBatchStride = 32;
-static_assert((kBatchMax - 1) * kBatchStride < (int)kTicketWords);
+// kOne: the grid is one block per chunk, and `ticket` has zero counters (left
+// zero).  The chunks of a call are counted on the call's own counter and
+// the block that arrives last folds them: no second launch.  A kernel of its
+// own: as a run-time branch it cost the two-launch form 9% (32 calls of up to
+// 2^24 int32: 97.9 -> 106.5 us).
+static_assert(kBatchMax <= (int)kTicketCounters);
 
 template <class FM, class F, class S, class Acc, int U, bool kOne>
   requires device_callable<F> && device_callable<FM>
@@ -201,7 +199,7 @@ __global__ __launch_bounds__(1024) void batch_kernel(FM fm, F f, BatchTable t, A
         last = 1;
         if (chunks > 1) {
           publish_partial(partials, c, tt);
-          last = arrive(ticket + i * kBatchStride, (uint32_t)chunks);
+          last = arrive(ticket + i * kTicketStride, (uint32_t)chunks);
         }
       }
       __syncthreads();

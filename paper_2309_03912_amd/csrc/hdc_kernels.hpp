@@ -374,8 +374,8 @@ __device__ __forceinline__ void fold_partials(Get get, int G, void* out, typenam
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t kTicketFan = 16;
-constexpr uint32_t kTicketStride = 64;                                 // 32-bit words between counters
-constexpr uint32_t kTicketWords = (kTicketFan + 1) * kTicketStride;    // one ticket: the root, then the fan
+constexpr uint32_t kTicketStride = 64;    // 32-bit words between a ticket's counters
+constexpr uint32_t kTicketCounters = 32;  // of one ticket: the root, then the fan; one per call of a batch
 
 // A fold state as machine words, and its agent-scope stores and loads.
 template <class Acc>

@@ -42,7 +42,7 @@ hdc_status launch_final(const Acc* partials, int64_t g, void* out, hipStream_t s
   return check_launch("final combine launch");
 }
 
-// `ticket`: kTicketWords zero words that no other work uses until this call
+// `ticket`: kTicketCounters zero counters that no other work uses until this call
 // completes; with it the reduction is one launch (its last block folds the
 // partials), without it (NULL) two launches.  Both fold in the same order, so
 // they give the same bits.

@@ -68,3 +68,32 @@ def test_same_bits_without_a_ticket():
                          capture_output=True, text=True, timeout=100)
     print(run.stdout[-2000:], run.stderr[-2000:])
     assert run.returncode == 0 and "SAME_BITS" in run.stdout
+
+
+MANY = r"""
+import torch
+import paper_2309_03912_amd as hdc
+
+x = torch.rand(100_000, device="cuda")
+out = torch.empty((), device="cuda")
+need = hdc.workspace_size(hdc.OP_TRANSFORM_REDUCE, hdc.F32, 0, 100_000)
+buf = torch.empty(need + 60_000 * 256, dtype=torch.uint8, device="cuda")
+want = hdc.transform_reduce(x, {"fn": "identity"}, "plain").item()
+got = torch.empty(60_000, device="cuda")
+for rep in range(2):  # twice: every ticket is back at 0
+    got.fill_(float("nan"))
+    for i in range(60_000):
+        hdc.transform_reduce(x, {"fn": "identity"}, "plain", out=got[i], ws=buf[256 * i:256 * i + need])
+    assert (got == want).all().item(), rep
+print("SAME_SUMS", flush=True)
+"""
+
+
+def test_sixty_thousand_workspaces_take_one_launch():
+    """A program whose workspaces change address (a caching allocator) keeps the one-launch form."""
+    run = subprocess.run([sys.executable, "-u", "-c", MANY], cwd=ROOT,
+                         env=dict(os.environ, PYTHONPATH=ROOT, HDC_LOG="1"), capture_output=True, text=True, timeout=100)
+    lines = [v for v in run.stderr.splitlines() if v.startswith("hdc: transform_reduce")]
+    print(run.stdout[-500:], run.stderr[-500:])
+    assert run.returncode == 0 and "SAME_SUMS" in run.stdout
+    assert len(lines) == 120_001 and all("schedule=one launch" in v for v in lines)

@@ -183,6 +183,7 @@ hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64
   tl.last = reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + half);
   tl.meta = tl.first + tl.cap;  // 8 of a slot's 32 bytes are its fold state
   tl.tile_vecs = tile / S::kVec;
+  tl.crowded = tile / kCrowdedLen < kMostEnds ? (int32_t)(tile / kCrowdedLen) : kMostEnds;
   int64_t tiles = total / tile + 2;  // at most: the head joins the first tile, the tail the last
   if (tiles > tl.cap) tiles = tl.cap;
   // by the sizes alone, not by whether a ticket is left: the passes and folds that follow give other bits
@@ -218,9 +219,29 @@ hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64
     seg_last_kernel<S, Acc><<<dim3(1), dim3(block), 0, st>>>((const T*)x, off, nseg, tl, out);
     return check_launch("segmented last-fold launch");
   }
-  int64_t gc = (nseg + 255) / 256;  // one wavefront per 64 segments
+  // Up to 8 wavefronts per compute unit, of at most 64 segments at a time: a
+  // wavefront folds its wide segments one by one (100 segments of 500,000 bf16
+  // in two wavefronts: 87 us a call, in a wavefront each 40).
+  const int64_t waves = (int64_t)cus * 8;
+  int32_t per = 1;
+  while (per < 64 && per * waves < nseg) per *= 2;
+  int64_t gc = ((nseg + per - 1) / per + 3) / 4;
+  // Parts of a crowded tile: its chunks one after another are a chain of 1.5 to
+  // 3 us each, a part costs three searches (~5 us).  As many as give the
+  // wavefronts four parts each if all segments lie in crowded tiles, of two
+  // chunks at least.
+  int32_t lg = 0;
+  if (!dense && nseg > tl.crowded) {
+    if (gc < waves / 4) gc = waves / 4;
+    while ((nseg / tl.crowded << (lg + 1)) <= 4 * waves && (tl.tile_vecs >> (lg + 1)) >= 128) ++lg;
+  }
   if (gc > (int64_t)cus * 8) gc = (int64_t)cus * 8;
-  seg_tiles_combine_kernel<S, Acc><<<dim3((unsigned)gc), dim3(256), 0, st>>>((const T*)x, off, nseg, tl, out);
+  const dim3 cgrid((unsigned)gc), cblock(256);
+  if (dense)
+    seg_tiles_combine_kernel<S, Acc><<<cgrid, cblock, 0, st>>>((const T*)x, off, nseg, per, tl, out);
+  else
+    seg_tiles_combine_crowded_kernel<F, S, Acc>
+        <<<cgrid, cblock, 0, st>>>(f, (const T*)x, off, nseg, per, lg, tl, out);
   return check_launch("segmented tile combine launch");
 }
 

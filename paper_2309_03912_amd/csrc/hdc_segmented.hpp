@@ -447,14 +447,24 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int64_t* __restr
 // ran through it (kTileThrough); and whether the tile wrote `last`.
 constexpr uint64_t kTileThrough = uint64_t(1) << 32;
 constexpr uint64_t kTileLast = uint64_t(1) << 33;
+// What a tile of the pass without the scan left to the second launch: the
+// segments inside it, if many of their ends are (TileWave::crowded).
+constexpr uint64_t kTileCrowded = uint64_t(1) << 34;
+// That many: one per kCrowdedLen elements of a tile, as far as a batch of 64
+// offsets reaches.  A tile of 8192 with 32 ends or more left to the second
+// launch made 1.34e8 f32 in lognormal segments of 1340 take 116 us, with 63 or
+// more 100.
+constexpr int kCrowdedLen = 128;
+constexpr int kMostEnds = 63;
 
 struct SegTiles {
   uint64_t* first;    // per tile: its part of the segment open at its start (a fold state's words)
   uint64_t* last;     // per tile: its part of a segment starting in it and running past its end
-  uint64_t* meta;     // per tile, with `one`: what it did
+  uint64_t* meta;     // per tile, with `one` or without the scan: what it did
   int64_t cap;        // tiles the workspace holds
   int64_t tile_vecs;  // 16-byte vectors per tile
   int32_t one;        // few tiles: one block folds the slots
+  int32_t crowded;    // segment ends inside a tile that make it crowded
 };
 
 // With `one` the slots are stored write-through at agent scope: the block that
@@ -560,7 +570,7 @@ struct SegFinder {
   int64_t probe;    // this lane's probe of the round in flight; INT64_MAX if none
 
   __device__ void issue(const int64_t* off, int32_t S, int lane) {
-    step = n > 64 ? (n - 1) / 64 + 1 : 1;  // n + 63 may not fit 32 bits
+    step = n > 64 ? (int32_t)(((uint32_t)n + 63u) / 64u) : 1;  // n + 63 may not fit 31 bits
     const int64_t idx = (int64_t)a + (int64_t)lane * step;
     const bool ok = step == 1 ? idx <= S : idx < (int64_t)a + n;
     probe = ok ? off[idx] : INT64_MAX;
@@ -664,8 +674,9 @@ struct TileWave {
   }
   // Before a step: a batch more than half used is reloaded from the current
   // segment on, so the boundaries of a step read their offsets from it.
+  // (Without the scan the batch holds every end inside the tile: run.)
   __device__ void refill() {
-    if (j - bbase >= 32) load_batch(j);
+    if (kDense && j - bbase >= 32) load_batch(j);
   }
 
   // The segment holding position `pos` (the last j with off[j] - off[0] <=
@@ -719,7 +730,7 @@ struct TileWave {
     nb = bound(j + 1);
     if (nb == b) {  // empty ones in between
       const int64_t pos = base + b;
-      if (read_lane(bnd, 63) > pos)
+      if (!kDense || read_lane(bnd, 63) > pos)
         j = bbase + __builtin_popcountll(__builtin_amdgcn_ballot_w64(bnd <= pos)) - 1;
       else
         search_on(pos);
@@ -854,8 +865,8 @@ struct TileWave {
       const int64_t s = bnd - base - cs;
       int64_t e = dpp_words<0x130, 0xF>(bnd) - base - cs;
       e = lane == 63 ? INT64_MAX : e;  // wave_shl:1 gives the next offset; lane 63 has none
-      const int64_t i = (int64_t)bbase + lane;
-      if (i >= j && e < ce - cs && e > s) {  // segment i ends inside the chunk and is not empty
+      const int32_t k = lane - (j - bbase);  // segment j + k
+      if (k >= 0 && e < ce - cs && e > s) {  // it ends inside the chunk and is not empty
         const int32_t p = (int32_t)e - 1;
         Acc v;
         if (p < 0) {
@@ -864,10 +875,10 @@ struct TileWave {
           v = lds->vals[p];
           if (s < (p & ~(KV - 1))) v = Acc::merge(lds->pre[p / KV], v);
         }
-        if (i == j && !started)
-          put(&st.first[tile], acc_word(v));
+        if (k > 0 || started)
+          store_result<Acc>(out, (int64_t)j + k, v);
         else
-          store_result<Acc>(out, i, v);
+          put(&st.first[tile], acc_word(v));
       }
       __builtin_amdgcn_wave_barrier();
       if (!more()) break;
@@ -907,6 +918,54 @@ struct TileWave {
     if (!mine) t[0] = Term{};
     split<1>(t, lane, [](int) { return 0; }, p0, p1);
     lane0 = false;
+  }
+
+  // A tile with st.crowded segment ends or more inside, in the pass without
+  // the scan (the mean segment is long: here lie many of the short ones, or the
+  // workspace is sized for far more elements than there are).  Split end by
+  // end by one wavefront, 60,000 segments of 4 elements on average took 420
+  // to 610 us of a call of 5e7 elements that takes 50 without them.  So it
+  // stores only the parts of the segments that it shares with other tiles; the
+  // segments inside it are the second launch's.
+  __device__ void crowded() {
+    const bool ends = !started;  // the segment open at the start ends at nb
+    int64_t s = base, e = ends ? base + nb : base;
+    uint64_t* to = &st.first[tile];
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+      if (e > s) {
+        // one vector per lane and round, one fold state: few registers
+        Acc a = Acc::zero();
+#pragma unroll 1
+        for (int64_t v0 = s; v0 < e; v0 += 64 * KV) {
+          const int64_t p = v0 + lane * KV;
+          Vec<S> d{};
+          if (p + KV <= e) {
+            d = load16<S>(x + p);
+          } else {
+#pragma unroll
+            for (int k = 0; k < KV; ++k)
+              if (p + k < e) d.e[k] = x[p + k];
+          }
+          Term t[KV];
+          terms<KV>(d.e, t);
+#pragma unroll
+          for (int k = 0; k < KV; ++k) a.add(p + k < e ? t[k] : Term{});
+        }
+        a = wave_reduce(a, MergeOp<Acc>{});
+        if (lane == 0) *to = acc_word(a);
+      }
+      if (k == 0) {
+        if (read_lane(bnd, 63) < base + len)  // the segment that holds the tile's end
+          search_on(base + len - 1);
+        else
+          j = bbase + __builtin_popcountll(__builtin_amdgcn_ballot_w64(bnd < base + len)) - 1;
+        s = read_lane(bnd, j - bbase);
+        e = bound(j + 1) > len ? base + len : s;  // it runs on, or lies inside
+        to = &st.last[tile];
+      }
+    }
+    if (lane == 0) st.meta[tile] = kTileCrowded;
   }
 
   // Tile position 0 of tile t, relative to off[0].
@@ -959,6 +1018,13 @@ struct TileWave {
     locate(fd);
     if (next >= 0) fd.start(off, S_, lo + tile_base(g, st.tile_vecs, next), lane);
     bool searching = next >= 0;
+    if constexpr (!kDense) {
+      if (j - bbase + st.crowded >= 64) load_batch(j);
+      if (read_lane(bnd, j - bbase + st.crowded) - base < len) {
+        crowded();
+        return;
+      }
+    }
     acc = Acc::zero();
     lane0 = true;
     ended = 0;
@@ -1042,7 +1108,11 @@ struct TileWave {
       if (lane == 0) put(&st.first[tile], acc_word(total));
       meta = kTileThrough;
     }
-    if (kDense && st.one && lane == 0) put(&st.meta[tile], meta | ended);
+    if constexpr (kDense) {
+      if (st.one && lane == 0) put(&st.meta[tile], meta | ended);
+    } else {
+      if (lane == 0) st.meta[tile] = 0;
+    }
   }
 };
 
@@ -1168,8 +1238,8 @@ __global__ __launch_bounds__(kTilesMaxBlock) void seg_tiles_kernel(F f, const el
   // the tile geometry (it needs no position yet).
   SegFinder fd{};
   fd.begin(off, (int32_t)S_, lane);
-  if (kDense && st.one) zero_empty<Acc>(off, S_, w, W, lane, out);
   const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
+  if (kDense && st.one) zero_empty<Acc>(off, S_, w, W, lane, out);
   if (g.ntiles == 0) return;
   // More tiles than the workspace holds: every segment is folded whole by
   // one wavefront.
@@ -1210,16 +1280,16 @@ __global__ __launch_bounds__(kTilesMaxBlock) void seg_last_kernel(const elem_t<S
 
 // Segments that span tiles (the second launch of many tiles): their parts folded in tile
 // order (the part of the tile where the segment starts, then every later
-// tile's `first` part).  Each lane takes one segment; a segment spanning more
-// than kLaneTiles tiles is folded by the whole wavefront (wave_fold_items).
+// tile's `first` part).  A wavefront takes `per` segments at a time (a power of
+// two), one per lane; a segment spanning more than kLaneTiles tiles is folded
+// by the whole wavefront (wave_fold_items), one after another.  So `per` is
+// small where there are few segments, and a wavefront's segments are runs of
+// eight from all over, not neighbours.
 constexpr int64_t kLaneTiles = 16;
 
 template <class S, class Acc>
-__global__ __launch_bounds__(256) void seg_tiles_combine_kernel(const elem_t<S>* __restrict__ x,
-                                                                const int64_t* __restrict__ off, int64_t S_,
-                                                                SegTiles st, void* out) {
-  const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
-  if (g.ntiles > st.cap) return;  // the tile pass folded every segment whole
+__device__ __forceinline__ void seg_combine_spans(const TileGeom& g, const int64_t* __restrict__ off, int64_t S_,
+                                                  int32_t per, const SegTiles& st, void* out) {
   constexpr bool kComp = std::is_same_v<Acc, CompAcc>;
   // part k of a segment whose first tile is ts
   auto part = [&](int64_t ts, int64_t k) {
@@ -1228,8 +1298,9 @@ __global__ __launch_bounds__(256) void seg_tiles_combine_kernel(const elem_t<S>*
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t j0 = wave * 64; j0 < S_; j0 += nwaves * 64) {
-    const int64_t j = j0 + lane;
+  const int32_t run = per < 8 ? per : 8;
+  for (int64_t b0 = 0; b0 < S_; b0 += nwaves * per) {
+    const int64_t j = lane < per ? b0 + ((int64_t)(lane / run) * nwaves + wave) * run + lane % run : S_;
     int64_t ts = 0, te = 0;
     if (j < S_) {
       const int64_t s = off[j] - g.lo, e = off[j + 1] - g.lo;
@@ -1254,16 +1325,93 @@ __global__ __launch_bounds__(256) void seg_tiles_combine_kernel(const elem_t<S>*
     }
     for (uint64_t mask = __builtin_amdgcn_ballot_w64(wide); mask; mask &= mask - 1) {  // uniform
       const int b = __builtin_ctzll(mask);
-      const int64_t bts = read_lane(ts, b), m = read_lane(te, b) - bts + 1;
+      const int64_t bts = read_lane(ts, b), m = read_lane(te, b) - bts + 1, bj = read_lane(j, b);
       if constexpr (kComp) {
         const double d = wave_fold_items<double>([&](int64_t k) { return comp_value(part(bts, k)); }, m, lane,
                                                  AddF64{}, 0.0);
-        if (lane == 0) static_cast<double*>(out)[j0 + b] = d;
+        if (lane == 0) static_cast<double*>(out)[bj] = d;
       } else {
         const Acc a = wave_fold_items<Acc>([&](int64_t k) { return part(bts, k); }, m, lane, MergeOp<Acc>{},
                                            Acc::zero());
-        if (lane == 0) store_result<Acc>(out, j0 + b, a);
+        if (lane == 0) store_result<Acc>(out, bj, a);
       }
+    }
+  }
+}
+
+// The second launch after the pass with the scan.
+template <class S, class Acc>
+__global__ __launch_bounds__(256) void seg_tiles_combine_kernel(const elem_t<S>* __restrict__ x,
+                                                                const int64_t* __restrict__ off, int64_t S_,
+                                                                int32_t per, SegTiles st, void* out) {
+  const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
+  if (g.ntiles > st.cap) return;  // the tile pass folded every segment whole
+  seg_combine_spans<S, Acc>(g, off, S_, per, st, out);
+}
+
+// The last j in [a, S] with off[j] <= p, given that off[a] <= p.
+__device__ __forceinline__ int32_t last_offset(const int64_t* off, int32_t S, int32_t a, int64_t p, int lane) {
+  SegFinder fd;
+  fd.aim(p);
+  fd.a = a;
+  fd.n = S + 1 - a;
+  fd.issue(off, S, lane);
+  while (!fd.final_round()) fd.next(off, S, lane);
+  return fd.a + __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < fd.n && fd.probe <= p)) - 1;
+}
+
+// The second launch after the pass without the scan: also the segments inside
+// crowded tiles, by the pass with the scan.  A wavefront takes the segments
+// that start in one of 2^lg parts of a tile: from the first of them to the end
+// of the last they are a range of their own, of one tile that no segment
+// leaves.  The parts go round the wavefronts, so that neighbours go to
+// different ones.
+
+template <class F, class S, class Acc>
+  requires device_callable<F>
+__global__ __launch_bounds__(256) void seg_tiles_combine_crowded_kernel(F f, const elem_t<S>* __restrict__ x,
+                                                                        const int64_t* __restrict__ off,
+                                                                        int64_t S_, int32_t per, int32_t lg,
+                                                                        SegTiles st, void* out) {
+  __shared__ DenseLds<S, Acc> dense_lds[4];
+  const TileGeom g = tile_geom<S>(x, off, S_, st.tile_vecs);
+  if (g.ntiles > st.cap) return;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int64_t w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + wid)), W = (int64_t)gridDim.x * 4;
+  const int64_t items = S_ > st.crowded ? g.ntiles << lg : 0;  // fewer segments crowd no tile
+  auto crowded = [&](int64_t i) { return i < items && (st.meta[i >> lg] & kTileCrowded) != 0; };
+  bool mine = crowded(w + lane * W);
+  seg_combine_spans<S, Acc>(g, off, S_, per, st, out);
+  for (int64_t i0 = w; i0 < items; i0 += 64 * W) {
+    if (i0 > w) mine = crowded(i0 + lane * W);
+    for (uint64_t mask = __builtin_amdgcn_ballot_w64(mine); mask; mask &= mask - 1) {  // uniform
+      const int64_t i = i0 + __builtin_ctzll(mask) * W;
+      const int64_t t = i >> lg, q = i & ((1 << lg) - 1);
+      const int64_t t0 = TileWave<F, S, Acc, 1, true>::tile_base(g, st.tile_vecs, t);
+      const int64_t t1 = t == g.ntiles - 1 ? g.n : TileWave<F, S, Acc, 1, true>::tile_base(g, st.tile_vecs, t + 1);
+      const int64_t p0 = t0 + (((t1 - t0) * q) >> lg), p1 = t0 + (((t1 - t0) * (q + 1)) >> lg);
+      // [s, e): from the first offset at or after p0 to the first at or after p1, if the tile holds it,
+      // else to the last one it holds (the segment that starts there leaves the tile)
+      const int32_t j0 = p0 > 0 ? last_offset(off, (int32_t)S_, 0, g.lo + p0 - 1, lane) : -1;
+      const int64_t s = off[(int64_t)j0 + 1] - g.lo;
+      const int32_t j1 = last_offset(off, (int32_t)S_, j0 < 0 ? 0 : j0, g.lo + (p1 < t1 ? p1 - 1 : t1), lane);
+      int64_t e = p1 < t1 ? off[(int64_t)j1 + 1] - g.lo : t1 + 1;
+      if (e > t1) e = off[j1] - g.lo;
+      if (s >= e) continue;
+      TileGeom r{};
+      r.lo = g.lo + s;
+      r.n = e - s;
+      const int64_t mis = (int64_t)((uintptr_t)(x + r.lo) % 16);
+      r.head = mis ? (16 - mis) / (int64_t)sizeof(elem_t<S>) : 0;
+      if (r.head > r.n) r.head = r.n;
+      r.nvec = (r.n - r.head) / S::kVec;
+      r.tail_start = r.head + r.nvec * S::kVec;
+      r.ntiles = 1;
+      SegTiles whole = st;
+      whole.tile_vecs = r.nvec;
+      SegFinder fd{};
+      TileWave<F, S, Acc, 1, true> tw{f, x + r.lo, off, r.lo, (int32_t)S_, whole, out, dense_lds + wid, lane, 0};
+      tw.run(r, fd, false, -1);
     }
   }
 }

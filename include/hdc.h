@@ -322,7 +322,10 @@ typedef struct hdc_batch_call {
  * call (the table is passed to the kernels by value, so the launches can be
  * recorded into a graph).  Workspace: hdc_workspace_size(HDC_OP_BATCH, dt, acc,
  * sum of n, count, ...).  Reduction results depend on the tuning of
- * HDC_OP_BATCH (chunk length), not on the batch composition.
+ * HDC_OP_BATCH, not on the batch composition: each call's chunk length is that
+ * of its own size bucket.  (The launch takes the other fields from the bucket
+ * of the calls' average n; of these only `block` changes bits, and the default
+ * and the shipped cache have one `block` for all buckets of a class of floats.)
  */
 hdc_status hdc_batch_map_reduce(const hdc_functor* f, const hdc_functor* g,
                                 hdc_dtype dt, hdc_accum acc,

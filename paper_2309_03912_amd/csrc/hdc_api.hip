@@ -208,12 +208,16 @@ void ensure_tuning_loaded() {
     // Grouped batches fold chunks of 16384 elements (one partial per chunk) by
     // blocks of 512.  Against 32768 by 256, us a call: one call of 2^16 f32
     // 11.9 -> 8.0, of 2^19 12.9 -> 8.4, of 2^22 19.4 -> 12.7; 32 of up to 2^22
-    // f32 37.5 -> 35.4, int32 37.2 -> 34.1.  Calls of 2^24 elements or more on
-    // average keep 32768 by 256 (one f16 compensated call of 2^26: 55 against 66).
+    // f32 37.5 -> 35.4, int32 37.2 -> 34.1.  A call of 2^24 elements or more
+    // takes chunks of 32768 (one f16 compensated call of 2^26: 58 against 67 us;
+    // 16 of 2^24 201 against 223).  The chunk goes by the call's own size and the
+    // block is the same for all, so that no result depends on the rest of the
+    // batch; 256 threads were no better for large calls (f32 plain 2^26: 109
+    // against 102 us, bf16 compensated 55 against 53, f16 55 to 58 either way).
     for (auto& per_dt : g_tune[HDC_OP_BATCH])
       for (auto& per_acc : per_dt)
         for (int b = 0; b < kBuckets; ++b) {
-          per_acc[b].block = b == 3 ? 256 : 512;
+          per_acc[b].block = 512;
           per_acc[b].chunk = b == 3 ? 32768 : 16384;
           per_acc[b].passes = 1;
         }
@@ -677,6 +681,11 @@ hdc_status hdc_batch_map_reduce(const hdc_functor* f, const hdc_functor* g, hdc_
   }
   hipStream_t st = (hipStream_t)stream;
   const Tuning t = tuning_for(HDC_OP_BATCH, dt, acc, total / count);
+  int chunk_of[kBuckets];  // by a call's own size
+  {
+    std::lock_guard<std::mutex> lock(g_tune_mu);
+    for (int b = 0; b < kBuckets; ++b) chunk_of[b] = g_tune[HDC_OP_BATCH][dt][acc][b].chunk;
+  }
   void* ws = nullptr;
   size_t need = batch_workspace_bytes(total, count);
   if (need < reduce_workspace_bytes()) need = reduce_workspace_bytes();  // as hdc_workspace_size asks for
@@ -690,16 +699,18 @@ hdc_status hdc_batch_map_reduce(const hdc_functor* f, const hdc_functor* g, hdc_
 
   // Groups of up to kBatchMax calls.
   int32_t grp[kBatchMax];
+  int chunk[kBatchMax];
   int ng = 0;
   char* wsb = static_cast<char*>(ws);  // groups run in stream order and share it
   auto flush = [&]() -> hdc_status {
     if (ng == 0) return HDC_OK;
-    const hdc_status r = run_batch(f, *g, dt, acc, calls, grp, ng, wsb, cap, ticket, t, st);
+    const hdc_status r = run_batch(f, *g, dt, acc, calls, grp, chunk, ng, wsb, cap, ticket, t, st);
     ng = 0;
     return r;
   };
   for (int32_t i = 0; i < count; ++i) {
-    grp[ng++] = i;
+    grp[ng] = i;
+    chunk[ng++] = chunk_of[bucket_of(calls[i].n)];
     if (ng == kBatchMax) HDC_TRY(flush());
   }
   return flush();

@@ -3,12 +3,13 @@
 // there are more chunks than compute units, one combine launch.  The call table is a by-value kernel argument (no host-to-device
 // copy, so the launches can be recorded into a graph as they are).
 //
-// Every call is cut into chunks of `chunk_vecs` 16-byte vectors; the global
-// chunk index space is the concatenation of all calls' chunks.  A block takes
+// Every call is cut into chunks of its `chunk_vecs` 16-byte vectors, which its
+// own size and the tuning set; the global chunk index space is the concatenation of all calls' chunks.  A block takes
 // chunks grid-stride, finds the call owning the chunk from the prefix table,
 // maps and folds it, and writes one partial per chunk.  The combine launch
 // folds each call's partials in chunk order, so results depend only on the
-// data and the chunk size: bit-reproducible.
+// data, the chunk size and the block: bit-reproducible, and the same whatever
+// other calls the batch holds.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,12 +29,12 @@ struct BatchCall {
   const void* x;
   void* y;  // nullptr: no map for this call
   void* out;
-  Range r;  // vector-mode walk of x (x and y share their 16-byte alignment)
+  Range r;  // the walk, aligned to y if the call maps, else to x; the other operand is read from wherever it starts
+  int64_t chunk_vecs;  // 16-byte vectors per chunk
 };
 
 struct BatchTable {
   int32_t count;
-  int64_t chunk_vecs;                 // 16-byte vectors per chunk
   int64_t prefix[kBatchMax + 1];      // first global chunk of each call
   BatchCall call[kBatchMax];
 };
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(1024) void batch_kernel(FM fm, F f, BatchTable t, A
 #pragma unroll
     for (int k = 0; k < KV; ++k) acc[k] = Acc::zero();
     const elem_t<S>* xv = x + r.head;
-    const int64_t vend = (lc + 1) * t.chunk_vecs < r.nvec ? (lc + 1) * t.chunk_vecs : r.nvec;
+    const int64_t vend = (lc + 1) * call.chunk_vecs < r.nvec ? (lc + 1) * call.chunk_vecs : r.nvec;
     // Int32 calls (a quarter-rate multiply per element) load and store
     // through raw buffer resources based at the step and ending at the
     // chunk's last vector (word 3 0x00020000: 32-bit data format, no swizzle;
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(1024) void batch_kernel(FM fm, F f, BatchTable t, A
         }
       }
     };
-    int64_t v0 = lc * t.chunk_vecs;
+    int64_t v0 = lc * call.chunk_vecs;
     for (; v0 + B * U <= vend; v0 += B * U) step(v0, std::true_type{});
     if (v0 < vend) step(v0, std::false_type{});
     if (lc == 0) {  // the first chunk also takes the unaligned head and tail

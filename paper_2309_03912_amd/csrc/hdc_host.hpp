@@ -199,14 +199,14 @@ inline int64_t grid_for(int64_t units, int64_t per_block, int cus, const Tuning&
 }
 
 
-// Chunk length (in 16-byte vectors) of a grouped batch: the tuning's element
-// count rounded up to a whole number of block steps, and never fewer than
+// Chunk length (in 16-byte vectors) of a call of a grouped batch: `chunk`
+// elements rounded up to a whole number of block steps, and never fewer than
 // kMinChunk elements, so a call of n elements has at most n / kMinChunk + 1
 // chunks (the bound batch_workspace_bytes is sized for).
-constexpr int64_t batch_chunk_vecs(const Tuning& t, int kvec) {
+constexpr int64_t batch_chunk_vecs(const Tuning& t, int chunk, int kvec) {
   const int64_t step = (int64_t)t.block * t.unroll;
   const int64_t min_vecs = (kMinChunk + kvec - 1) / kvec;
-  int64_t v = t.chunk / kvec;
+  int64_t v = chunk / kvec;
   if (v < min_vecs) v = min_vecs;
   return (v + step - 1) / step * step;
 }
@@ -238,10 +238,11 @@ hdc_status run_segmented(const hdc_functor& f, hdc_dtype dt, const void* x, cons
                          int64_t total, hdc_accum acc, void* out, void* ws, size_t ws_bytes, uint32_t* ticket,
                          const Tuning& t, hipStream_t st);
 // `ws_bytes` is the workspace's capacity; a group whose chunk partials do not
-// fit is refused (HDC_ERR_WORKSPACE) before anything is launched.
+// fit is refused (HDC_ERR_WORKSPACE) before anything is launched.  `chunk`:
+// elements per chunk of each of the cnt calls.
 hdc_status run_batch(const hdc_functor* fm, const hdc_functor& g, hdc_dtype dt, hdc_accum acc,
-                     const hdc_batch_call* calls, const int32_t* idx, int cnt, void* ws, size_t ws_bytes,
-                     uint32_t* ticket, const Tuning& t, hipStream_t st);
+                     const hdc_batch_call* calls, const int32_t* idx, const int* chunk, int cnt, void* ws,
+                     size_t ws_bytes, uint32_t* ticket, const Tuning& t, hipStream_t st);
 
 // `slot`: see launch_scan; NULL: the look-back nodes go to the workspace.
 hdc_status run_scan(const hdc_functor& f, hdc_dtype dt, const void* x, void* y, int64_t n, hdc_accum acc,

@@ -309,13 +309,12 @@ hdc_status launch_segmented(const F& f, const void* x, const int64_t* off, int64
 
 template <class FM, class F, class S, class Acc>
 hdc_status launch_batch(const FM& fm, bool maps, const F& f, const hdc_batch_call* calls, const int32_t* idx,
-                        int cnt, void* ws, size_t ws_bytes, uint32_t* ticket, const Tuning& t,
+                        const int* chunk, int cnt, void* ws, size_t ws_bytes, uint32_t* ticket, const Tuning& t,
                         hipStream_t st) {
   int cus = 0;
   HDC_TRY(compute_units(&cus));
   BatchTable tab{};
   tab.count = cnt;
-  tab.chunk_vecs = batch_chunk_vecs(t, S::kVec);
   int64_t acc_chunks = 0, most = 0;  // of all calls, of one call
   for (int q = 0; q < cnt; ++q) {
     const hdc_batch_call& c = calls[idx[q]];
@@ -324,9 +323,10 @@ hdc_status launch_batch(const FM& fm, bool maps, const F& f, const hdc_batch_cal
     b.y = maps ? c.y : nullptr;
     b.out = c.out;
     b.r = make_range<S>(b.y ? b.y : c.x, c.n);
+    b.chunk_vecs = batch_chunk_vecs(t, chunk[q], S::kVec);
     tab.prefix[q] = acc_chunks;
     if (c.n > 0) {
-      int64_t nc = (b.r.nvec + tab.chunk_vecs - 1) / tab.chunk_vecs;
+      int64_t nc = (b.r.nvec + b.chunk_vecs - 1) / b.chunk_vecs;
       acc_chunks += nc > 0 ? nc : 1;
       if (nc > most) most = nc;
     }

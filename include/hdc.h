@@ -156,7 +156,14 @@ hdc_status hdc_map(const hdc_functor* f, hdc_dtype dt, const void* x, void* y,
  *   (COMPENSATED, EXACT) or int64 (EXACT_INT), all caller-owned.
  *   workspace: device scratch of at least hdc_workspace_size(...) bytes, or
  *   NULL to use a library-owned buffer (per device and stream, grown outside
- *   graph capture only).  Errors: HDC_ERR_INVALID_ARGUMENT (NULL or
+ *   graph capture only).  Calls that share a workspace must be ordered, as if
+ *   on one stream; a replay of a captured call counts as a call.  The library
+ *   keeps counters and look-back nodes for each workspace and stream (of a
+ *   captured call: the capture stream) that every call leaves ready for the
+ *   next one.  Calls that overlap on them give wrong results, and can leave
+ *   them so that later calls with that workspace and stream do too (a scan
+ *   then reports it through hdc_scan_status).  This holds for every entry
+ *   point with a workspace.  Errors: HDC_ERR_INVALID_ARGUMENT (NULL or
  *   misaligned pointers, n < 0), HDC_ERR_UNSUPPORTED (functor / dtype /
  *   accumulation not provided), HDC_ERR_WORKSPACE (workspace too small, or
  *   the library buffer would have to grow under capture).
@@ -183,7 +190,9 @@ hdc_status hdc_transform_reduce(const hdc_functor* f, hdc_dtype dt,
  *   a device looks up the scratch array's device address (no allocation).
  *   Every call on one device shares that device's scratch: calls that may
  *   overlap in time on one device (different streams, or graphs replayed
- *   concurrently) race and give wrong results.  Order them on one stream.
+ *   concurrently) race and give wrong results, and overlapping replays of
+ *   graphs captured on one stream can spoil later calls too (below).  Order
+ *   them on one stream.
  *   The scratch keeps the last call's partials; nothing in it needs to start
  *   at zero (each call writes every partial it reads).
  */

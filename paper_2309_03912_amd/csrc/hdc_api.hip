@@ -343,9 +343,11 @@ hdc_status scratch_address(void** out) {
 // The tickets are library-owned device memory (an object of static storage,
 // so zero-initialized when the code object is loaded), one per workspace
 // buffer and stream: calls on one stream are ordered, so they never use a
-// ticket at the same time, and calls that wrongly share a workspace across
+// ticket at the same time, and eager calls that wrongly share a workspace across
 // streams can spoil each other's partials but not a ticket, which later calls
-// rely on.  Once every slot of a device is taken, calls with a new workspace
+// rely on.  (Graphs hold the ticket of the stream they were captured on: two of
+// one workspace and capture stream that are wrongly replayed at once share it,
+// and can leave it at another count than 0.)  Once every slot of a device is taken, calls with a new workspace
 // or stream use the two-launch form.  There are 65,536 of them, in 8 MiB:
 // kTicketGroups groups of kTicketStride tickets, whose counters interleave (a
 // counter of every ticket of the group in one 256-byte line).  The first

@@ -996,6 +996,14 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   __syncthreads();
   const int64_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)tile_sh);
   lb.tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)tag_sh);
+  // A slot's ticket counts past the grid only after calls that overlapped on
+  // one workspace and stream (two graphs captured there, replayed at once):
+  // such a tile has no nodes.
+  if (tile >= (int64_t)gridDim.x) {
+    if (threadIdx.x == 0)
+      __hip_atomic_store(lb.status, gave_up_mark(lb), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
   auto w = scan_wave_at<F, S, Acc, E>(tile, n);
   w.template load<kEven>(x, seg);
   if constexpr (IsSeg<Acc>::value)

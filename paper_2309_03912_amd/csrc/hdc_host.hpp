@@ -199,14 +199,14 @@ inline int64_t grid_for(int64_t units, int64_t per_block, int cus, const Tuning&
 }
 
 
-// Chunk length (in 16-byte vectors) of a call of a grouped batch: `chunk`
-// elements rounded up to a whole number of block steps, and never fewer than
-// kMinChunk elements, so a call of n elements has at most n / kMinChunk + 1
+// Chunk length (in 16-byte vectors) of a call of a grouped batch: the tuning's
+// element count (of the call's own size) rounded up to a whole number of block
+// steps, and never fewer than kMinChunk elements, so a call of n elements has at most n / kMinChunk + 1
 // chunks (the bound batch_workspace_bytes is sized for).
-constexpr int64_t batch_chunk_vecs(const Tuning& t, int chunk, int kvec) {
+constexpr int64_t batch_chunk_vecs(const Tuning& t, int kvec) {
   const int64_t step = (int64_t)t.block * t.unroll;
   const int64_t min_vecs = (kMinChunk + kvec - 1) / kvec;
-  int64_t v = chunk / kvec;
+  int64_t v = t.chunk / kvec;
   if (v < min_vecs) v = min_vecs;
   return (v + step - 1) / step * step;
 }

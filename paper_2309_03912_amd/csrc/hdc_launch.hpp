@@ -323,7 +323,9 @@ hdc_status launch_batch(const FM& fm, bool maps, const F& f, const hdc_batch_cal
     b.y = maps ? c.y : nullptr;
     b.out = c.out;
     b.r = make_range<S>(b.y ? b.y : c.x, c.n);
-    b.chunk_vecs = batch_chunk_vecs(t, chunk[q], S::kVec);
+    Tuning own = t;
+    own.chunk = chunk[q];
+    b.chunk_vecs = batch_chunk_vecs(own, S::kVec);
     tab.prefix[q] = acc_chunks;
     if (c.n > 0) {
       int64_t nc = (b.r.nvec + b.chunk_vecs - 1) / b.chunk_vecs;

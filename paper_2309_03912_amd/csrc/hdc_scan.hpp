@@ -724,9 +724,11 @@ constexpr int64_t kScanSlotWords = 16 + 3 * (kScanSlotTiles + kScanSlotTiles / 6
 constexpr int64_t kScanLongTiles = 1 << 14;
 
 // What a slot launch that gave up leaves in the status word (its own mark, so
-// that the first tile can clear an earlier call's word at any time).
+// that the first tile can clear an earlier call's word at any time).  The small
+// and the long slot of a workspace count their launches apart, so the slot's
+// address is in the mark too.
 __device__ __forceinline__ uint32_t gave_up_mark(const ScanLB& lb) {
-  return lb.ticket64 ? (lb.tag * 2654435761u) | 1u : 1u;
+  return lb.ticket64 ? ((lb.tag ^ (uint32_t)((uintptr_t)lb.ticket64 >> 7)) * 2654435761u) | 1u : 1u;
 }
 
 constexpr uint32_t kLookbackSpinLimit = 1u << 16;  // polls before giving up

@@ -9,3 +9,9 @@ if ROOT not in sys.path:
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs an MI355X (gfx950) GPU")
     config.addinivalue_line("markers", "slow: long CPU test")
+
+
+def pytest_collection_modifyitems(items):
+    # uses up the process's look-back slots for long scans: the tests of other
+    # files come before it and run with a slot
+    items.sort(key=lambda item: item.path.name == "test_gpu_scan_long_slots.py")

@@ -214,7 +214,11 @@ def workspace_size(op: int, dtype: int, acc: int, n: int, num_segments: int = 0)
 
 
 def workspace(device, op: int, dtype: int, acc: int, n: int, num_segments: int = 0) -> torch.Tensor:
-    """A cached device workspace for the current stream of ``device``, large enough for the call."""
+    """A cached device workspace for the current stream of ``device``, large enough for the call.
+
+    For the segmented reduce it is as large as the call needs and no larger: the library takes the
+    elements it plans for from the size, so a buffer grown by earlier calls would change the schedule,
+    the time and the last bits of a floating-point result."""
     need = workspace_size(op, dtype, acc, n, num_segments)
     stream = torch.cuda.current_stream(device).cuda_stream
     key = (torch.device(device).index, stream)
@@ -223,7 +227,7 @@ def workspace(device, op: int, dtype: int, acc: int, n: int, num_segments: int =
         # zero-filled on first allocation; every kernel leaves it reusable
         ws = torch.zeros(max(need, 256), dtype=torch.uint8, device=device)
         _workspaces[key] = ws
-    return ws
+    return ws[:need] if op == OP_SEGMENTED_REDUCE else ws
 
 
 # ---------------------------------------------------------------------------

@@ -2,12 +2,16 @@
 
 For each tuning class (op, dtype, accumulation, size bucket) it times every
 candidate setting of (block, unroll, grid_mult) -- then, for the segmented op,
-(chunk, small_seg, seg_per_wave), and for the reductions one or two launches
-(passes) -- on a synthetic workload of that class:
+(chunk, small_seg, seg_per_wave), for the reductions one or two launches
+(passes), and for batches both chunk and passes -- on a synthetic workload of
+that class:
 
-  * HIP events on the launching stream, `reps` calls per measurement, median
-    of `rounds` measurements; candidates are interleaved round by round so
-    that clock or thermal drift hits all of them alike;
+  * a stream of calls on inputs and outputs that take turns, as many copies as
+    fill twice the last-level cache (eight at most), so that small calls are
+    timed with their launches and none on data that its last call left cached;
+  * HIP events on the launching stream, a millisecond or `reps` calls per
+    measurement, median of `rounds` measurements; candidates are interleaved
+    round by round so that clock or thermal drift hits all of them alike;
   * the best three are re-timed with twice the rounds before one is chosen;
   * every candidate's output must agree with the others: maps bit for bit,
     integer sums exactly, floating-point sums within the library tolerance
@@ -16,7 +20,9 @@ candidate setting of (block, unroll, grid_mult) -- then, for the segmented op,
 
 The winners are written as a tuning cache (one line per class:
 "op dtype acc bucket block unroll grid_mult chunk small_seg seg_per_wave passes"),
-which the library reads through hdc_load_tuning / HDC_TUNE_CACHE.
+which the library reads through hdc_load_tuning / HDC_TUNE_CACHE.  Classes
+that a run does not tune keep their lines of the output file (--fresh drops
+them).
 
     python -m paper_2309_03912_amd.autotune --out paper_2309_03912_amd/tuning_gfx950.txt
 """
@@ -53,6 +59,9 @@ def _inputs(dt, n, dev, seed=1):
     return (x * 2.0 ** -23).to(TORCH_DT[dt]).to(dev)
 
 
+COPY_BYTES = 512 << 20  # twice the last-level cache
+
+
 def _time(fn, reps):
     s = torch.cuda.Event(enable_timing=True)
     e = torch.cuda.Event(enable_timing=True)
@@ -70,76 +79,82 @@ class Case:
     def __init__(self, op, dt, acc, n, dev, segments=None):
         self.op, self.dt, self.acc, self.n = op, dt, acc, n
         self.bucket = tuning_bucket(n)
-        self.x = _inputs(dt, n, dev)
-        coef = [1.0 / (k + 1) for k in range(9)]
-        self.horner = {"fn": "horner", "coef": coef}
+        self.horner = {"fn": "horner", "coef": [1.0 / (k + 1) for k in range(9)]}
         self.aff = {"fn": "affine", "a": 3, "b": -7} if dt == I32 else {"fn": "affine", "a": 2.5, "b": 0.5}
         self.ident = {"fn": "identity"}
-        self.y = torch.empty_like(self.x)
-        accname = {ACC_PLAIN: "plain", ACC_COMPENSATED: "compensated", ACC_EXACT_INT: "exact_int",
-                   ACC_EXACT: "exact"}[acc]
-        self.accname = accname
-        if op == OP_BATCH:
-            # `segments` holds the call sizes of the batch
-            self.xs = [_inputs(dt, m, dev, seed=10 + i) for i, m in enumerate(segments)]
-            self.ys = [torch.empty_like(v) for v in self.xs]
-            self.outs = [torch.empty((), dtype={ACC_PLAIN: torch.float32, ACC_COMPENSATED: torch.float64,
-                                                ACC_EXACT_INT: torch.int64}[acc], device=dev) for _ in self.xs]
-            self.ws = workspace(dev, op, dt, acc, sum(segments), len(segments))
-            self.bucket = tuning_bucket(n)
-        elif op == OP_SCAN:
-            self.ys = torch.empty(n, dtype={ACC_PLAIN: torch.float32, ACC_COMPENSATED: torch.float64,
-                                            ACC_EXACT_INT: torch.int64}[acc], device=dev)
-            self.ws = workspace(dev, op, dt, acc, n)
-        elif op == OP_SEGMENTED_REDUCE:
-            self.off = segments.to(dev)
-            S = self.off.numel() - 1
-            self.ws = workspace(dev, op, dt, acc, n, S)
-            self.out = torch.empty(S, dtype={ACC_PLAIN: torch.float32, ACC_COMPENSATED: torch.float64,
-                                             ACC_EXACT_INT: torch.int64}[acc], device=dev)
-        elif op != OP_MAP:
-            self.ws = workspace(dev, op, dt, acc, n)
-            self.out = torch.empty((), dtype={ACC_PLAIN: torch.float32, ACC_COMPENSATED: torch.float64,
-                                              ACC_EXACT_INT: torch.int64, ACC_EXACT: torch.float64}[acc],
-                                   device=dev)
-        if op == OP_DOT:
-            self.z = _inputs(dt, n, dev, seed=2)
+        self.accname = {ACC_PLAIN: "plain", ACC_COMPENSATED: "compensated", ACC_EXACT_INT: "exact_int",
+                        ACC_EXACT: "exact"}[acc]
+        total = sum(segments) if op == OP_BATCH else n  # of a batch, `segments` holds the call sizes
+        size = {F32: 4, I32: 4}.get(dt, 2)
+        out_size = {OP_MAP: size, OP_MAP_REDUCE: size, OP_BATCH: size, OP_DOT: size, OP_SCAN: 8}.get(op, 0)
+        copies = max(1, min(8, COPY_BYTES // (total * (size + out_size))))
+        self.off = segments.to(dev) if op == OP_SEGMENTED_REDUCE else None
+        parts = len(segments) if op == OP_BATCH else self.off.numel() - 1 if self.off is not None else 0
+        self.ws = None if op == OP_MAP else workspace(dev, op, dt, acc, total, parts)
+        self.sets = [self._set(c, segments, dev) for c in range(copies)]
+        self.at = 0
+        # calls per measurement: about a millisecond of them
+        self.reps = 5 if total >= 1 << 24 else 40 if total >= 1 << 20 else 200
+
+    def _set(self, copy, segments, dev):
+        """Inputs and outputs of one copy (copy 0's are the ones that output() reads)."""
+        odt = {ACC_PLAIN: torch.float32, ACC_COMPENSATED: torch.float64, ACC_EXACT_INT: torch.int64,
+               ACC_EXACT: torch.float64}[self.acc]
+        s = argparse.Namespace()
+        if self.op == OP_BATCH:
+            s.x = [_inputs(self.dt, m, dev, seed=10 + i + 100 * copy) for i, m in enumerate(segments)]
+            s.y = [torch.empty_like(v) for v in s.x]
+            s.out = [torch.empty((), dtype=odt, device=dev) for _ in s.x]
+            return s
+        s.x = _inputs(self.dt, self.n, dev, seed=1 + 100 * copy)
+        if self.op in (OP_MAP, OP_MAP_REDUCE):
+            s.y = torch.empty_like(s.x)
+        elif self.op == OP_SCAN:
+            s.y = torch.empty(self.n, dtype=odt, device=dev)
+        if self.op == OP_DOT:
+            s.z = _inputs(self.dt, self.n, dev, seed=2 + 100 * copy)
+        if self.op == OP_SEGMENTED_REDUCE:
+            s.out = torch.empty(self.off.numel() - 1, dtype=odt, device=dev)
+        elif self.op not in (OP_MAP, OP_SCAN):
+            s.out = torch.empty((), dtype=odt, device=dev)
+        return s
 
     def run(self):
+        """One call, on the next copy."""
+        s = self.sets[self.at]
+        self.at = (self.at + 1) % len(self.sets)
+        fn = self.ident if self.dt == I32 or self.acc == ACC_EXACT else self.horner
         if self.op == OP_BATCH:
-            fn = self.ident if self.dt == I32 else self.horner
-            batch_map_reduce(self.xs, self.aff, fn, self.accname, ys=self.ys, outs=self.outs, ws=self.ws)
-            return
-        if self.op == OP_SCAN:
-            fn = self.ident if self.dt == I32 else self.horner
-            scan(self.x, fn, self.accname, out=self.ys, ws=self.ws, check=False)  # checked in output()
-            return
-        if self.op == OP_MAP:
-            hdc_map(self.x, self.aff, out=self.y)
+            batch_map_reduce(s.x, self.aff, fn, self.accname, ys=s.y, outs=s.out, ws=self.ws)
+        elif self.op == OP_SCAN:
+            scan(s.x, fn, self.accname, out=s.y, ws=self.ws, check=False)  # checked in output()
+        elif self.op == OP_MAP:
+            hdc_map(s.x, self.aff, out=s.y)
         elif self.op == OP_TRANSFORM_REDUCE:
-            fn = self.ident if self.dt == I32 or self.acc == ACC_EXACT else self.horner
-            transform_reduce(self.x, fn, self.accname, out=self.out, ws=self.ws)
+            transform_reduce(s.x, fn, self.accname, out=s.out, ws=self.ws)
         elif self.op == OP_DOT:
-            transform_reduce(self.x, {"fn": "product"}, self.accname, z=self.z, out=self.out, ws=self.ws)
+            transform_reduce(s.x, {"fn": "product"}, self.accname, z=s.z, out=s.out, ws=self.ws)
         elif self.op == OP_MAP_REDUCE:
-            fn = self.ident if self.dt == I32 else self.horner
-            map_reduce(self.x, self.aff, fn, self.accname, out=self.y, result=self.out, ws=self.ws)
+            map_reduce(s.x, self.aff, fn, self.accname, out=s.y, result=s.out, ws=self.ws)
         else:
-            fn = self.ident if self.dt == I32 else self.horner
-            segmented_reduce(self.x, self.off, fn, self.accname, out=self.out, ws=self.ws)
+            segmented_reduce(s.x, self.off, fn, self.accname, out=s.out, ws=self.ws)
 
     def output(self):
+        """The outputs of a call on copy 0."""
+        self.at = 0
+        self.run()
+        s = self.sets[0]
         if self.op == OP_BATCH:
-            return ([y.clone() for y in self.ys], [o.clone() for o in self.outs])
+            return ([y.clone() for y in s.y], [o.clone() for o in s.out])
         if self.op == OP_SCAN:
             if scan_status(self.ws) != 0:
                 raise RuntimeError(f"a single-pass scan gave up on {self.key()}: its output is invalid")
-            return self.ys.clone()
+            return s.y.clone()
         if self.op == OP_MAP:
-            return self.y.clone()
+            return s.y.clone()
         if self.op == OP_MAP_REDUCE:
-            return (self.y.clone(), self.out.clone())
-        return self.out.clone()
+            return (s.y.clone(), s.out.clone())
+        return s.out.clone()
 
     def agrees(self, a, b):
         if self.op == OP_BATCH:
@@ -174,9 +189,9 @@ def candidates(op, quick=False):
     gms = [4, 8, 16] if quick else [2, 4, 8, 16, 32, 64]
     base = [dict(block=b, unroll=u, grid_mult=g) for b, u, g in itertools.product(blocks, unrolls, gms)]
     if op == OP_BATCH:
-        return base, [dict(chunk=c) for c in [8192, 16384, 32768, 65536]]
+        return base, [dict(chunk=c, passes=p) for c in [8192, 16384, 32768, 65536] for p in (1, 2)]
     if op == OP_SCAN:  # tile size x schedule (unroll 1: three passes, else one pass)
-        return [dict(block=b, unroll=u) for b in [256, 512, 1024] for u in [1, 4]]
+        return [dict(block=b, unroll=u) for b in [256, 512, 768, 1024] for u in [1, 4]]
     if op in (OP_TRANSFORM_REDUCE, OP_DOT, OP_MAP_REDUCE):  # geometry, then one or two launches
         return base, [dict(passes=p) for p in (1, 2)]
     if op != OP_SEGMENTED_REDUCE:
@@ -185,7 +200,8 @@ def candidates(op, quick=False):
            for c, s, w in itertools.product([2048, 4096, 8192] if quick else [1024, 2048, 4096, 8192, 16384],
                                             [64, 128, 256, 512], [2, 4, 8, 16] if quick else [1, 2, 4, 8, 16, 32, 64])]
     # per schedule (tiled, planned): the geometry at the default split, then the split (tile length for
-    # the tiled schedule; piece length and small-segment packing for the planned one)
+    # the tiled schedule, which halves it where there are few tiles, so that several lengths can be the
+    # same; piece length and small-segment packing for the planned one)
     return base, seg
 
 
@@ -202,7 +218,7 @@ def tune_case(case: Case, quick=False, reps=5, rounds=3, log=print):
         for _ in range(2 * rounds):
             for i, w in enumerate(wins):
                 set_tuning(op, dt, acc, b, **w)
-                times[i].append(_time(case.run, reps))
+                times[i].append(_time(case.run, max(reps, case.reps)))
         best = wins[min(times, key=lambda i: statistics.median(times[i]))]
         set_tuning(op, dt, acc, b, **best)
         log(json.dumps({"class": case.key(), "schedules": [
@@ -240,14 +256,14 @@ def _tune_stages(case: Case, quick, reps, rounds, log):
                         ref = out
                     elif not case.agrees(ref, out):
                         raise RuntimeError(f"candidate {trial[i]} disagrees with {trial[0]} on {case.key()}")
-                times[i].append(_time(case.run, reps))
+                times[i].append(_time(case.run, max(reps, case.reps)))
         med = {i: statistics.median(v) for i, v in times.items()}
         top = sorted(med, key=med.get)[:3]
         re = {i: [] for i in top}
         for r in range(2 * rounds):
             for i in top:
                 set_tuning(op, dt, acc, b, **trial[i])
-                re[i].append(_time(case.run, reps))
+                re[i].append(_time(case.run, max(reps, case.reps)))
         win = min(top, key=lambda i: statistics.median(re[i]))
         best = trial[win]
         set_tuning(op, dt, acc, b, **best)
@@ -257,40 +273,42 @@ def _tune_stages(case: Case, quick, reps, rounds, log):
     return best
 
 
-def default_cases(dev, quick=False, log2n=28):
-    """The classes the workloads of this project use, at their sizes."""
-    import synth  # seeded generators of the workloads (segment lengths)
+SIZES = [1 << 14, 1 << 18, 1 << 22]  # one per size bucket below the largest
+FOLDS = [(F32, ACC_PLAIN), (F32, ACC_COMPENSATED), (F16, ACC_COMPENSATED), (BF16, ACC_COMPENSATED), (I32, ACC_EXACT_INT)]
+
+
+def default_classes(quick=False, log2n=28):
+    """The classes of this project's workloads, as (op, dtype, accumulation, n) -- n of a batch is the
+    average call's -- largest sizes first."""
     n = 1 << log2n
-    cases = [
-        Case(OP_MAP, F32, ACC_PLAIN, n, dev),
-        Case(OP_MAP, I32, ACC_PLAIN, n, dev),
-        Case(OP_TRANSFORM_REDUCE, F32, ACC_PLAIN, n, dev),
-        Case(OP_TRANSFORM_REDUCE, I32, ACC_EXACT_INT, n, dev),
-        Case(OP_TRANSFORM_REDUCE, BF16, ACC_COMPENSATED, n, dev),
-        Case(OP_TRANSFORM_REDUCE, F16, ACC_COMPENSATED, n, dev),
-        Case(OP_TRANSFORM_REDUCE, F32, ACC_COMPENSATED, n, dev),
-        Case(OP_TRANSFORM_REDUCE, BF16, ACC_EXACT, n, dev),
-        Case(OP_TRANSFORM_REDUCE, F16, ACC_EXACT, n, dev),
-        Case(OP_DOT, F32, ACC_PLAIN, n, dev),
-        Case(OP_DOT, BF16, ACC_COMPENSATED, n, dev),
-        Case(OP_DOT, F16, ACC_COMPENSATED, n, dev),
-        Case(OP_DOT, F16, ACC_EXACT, n, dev),
-    ]
-    L = synth.segment_lengths(synth.seed_of(4))
-    off = synth.offsets_from_lengths(L)
-    cases += [Case(OP_SEGMENTED_REDUCE, F32, ACC_PLAIN, int(off[-1]), dev, off),
-              Case(OP_SEGMENTED_REDUCE, F32, ACC_COMPENSATED, int(off[-1]), dev, off)]
-    # the 64-call graph workload as two grouped batches (fp16 and int32 halves)
-    sizes = synth.call_sizes(synth.seed_of(5))
-    cases += [Case(OP_BATCH, F16, ACC_COMPENSATED, sum(sizes[0::2]) // 32, dev, sizes[0::2]),
-              Case(OP_BATCH, I32, ACC_EXACT_INT, sum(sizes[1::2]) // 32, dev, sizes[1::2])]
-    cases += [Case(OP_SCAN, F32, ACC_PLAIN, n, dev), Case(OP_SCAN, F32, ACC_COMPENSATED, n, dev),
-              Case(OP_SCAN, I32, ACC_EXACT_INT, n, dev)]
-    # batched calls: every size bucket of the fused map + reduce
-    for m in ([1 << 14, 1 << 18, 1 << 22, 1 << 25] if not quick else [1 << 18, 1 << 25]):
-        cases += [Case(OP_MAP_REDUCE, F16, ACC_COMPENSATED, m, dev), Case(OP_MAP_REDUCE, I32, ACC_EXACT_INT, m, dev),
-                  Case(OP_MAP, F16, ACC_PLAIN, m, dev), Case(OP_TRANSFORM_REDUCE, F16, ACC_COMPENSATED, m, dev)]
-    return cases
+    exact = [(F16, ACC_EXACT), (BF16, ACC_EXACT)]
+    dots = [(F32, ACC_PLAIN), (F16, ACC_COMPENSATED), (BF16, ACC_COMPENSATED), (F16, ACC_EXACT)]
+    small = [SIZES[1]] if quick else SIZES
+    classes = [(OP_MAP, dt, ACC_PLAIN, m) for m in [n] + small for dt in (F32, F16, BF16, I32)]
+    classes += [(OP_TRANSFORM_REDUCE, dt, acc, m) for m in [n] + small for dt, acc in FOLDS + exact]
+    classes += [(OP_DOT, dt, acc, m) for m in [n] + small for dt, acc in dots]
+    classes += [(OP_SEGMENTED_REDUCE, dt, acc, m) for m in [n // 2] + small for dt, acc in FOLDS]
+    classes += [(OP_MAP_REDUCE, dt, acc, m) for m in [n // 8] + small for dt, acc in FOLDS]
+    # the 64-call graph workload's halves (2^22 elements a call on average); and 32 large calls
+    classes += [(OP_BATCH, dt, acc, m) for m in (1 << 24, 1 << 22) for dt, acc in FOLDS]
+    classes += [(OP_SCAN, dt, acc, n) for dt, acc in FOLDS]
+    return classes
+
+
+def make_case(op, dt, acc, n, dev):
+    """The workload of a class."""
+    import synth  # seeded generators of the workloads (segment lengths, call sizes)
+    if op == OP_SEGMENTED_REDUCE:
+        off = synth.offsets_from_lengths(synth.segment_lengths(synth.seed_of(4)))
+        if off[-1] > n:  # the workload's first segments, as many as hold n elements
+            off = torch.cat([off[off < n], torch.tensor([n], dtype=off.dtype)])
+        return Case(op, dt, acc, int(off[-1]), dev, off)
+    if op == OP_BATCH:
+        if n >= 1 << 24:
+            return Case(op, dt, acc, n, dev, [n] * 32)
+        sizes = synth.call_sizes(synth.seed_of(5))[1 if dt == I32 else 0::2]
+        return Case(op, dt, acc, sum(sizes) // len(sizes), dev, sizes)
+    return Case(op, dt, acc, n, dev)
 
 
 def write_cache(path, results):
@@ -320,16 +338,20 @@ def main(argv=None):
     p.add_argument("--quick", action="store_true")
     p.add_argument("--log2n", type=int, default=28)
     p.add_argument("--ops", default="", help="comma-separated op ids to tune (default: all)")
-    p.add_argument("--merge", default="", help="cache file whose other classes are kept in the output")
+    p.add_argument("--merge", default="", help="cache file whose other classes are kept in the output (default: it)")
+    p.add_argument("--fresh", action="store_true", help="keep no other classes")
     a = p.parse_args(argv)
     dev = torch.device("cuda", 0)
     t0 = time.time()
-    results = read_cache(a.merge) if a.merge else {}
+    keep = a.merge or a.out
+    results = read_cache(keep) if not a.fresh and os.path.exists(keep) else {}
     ops = {int(o) for o in a.ops.split(",")} if a.ops else None
     tuned = set()
-    for case in default_cases(dev, a.quick, a.log2n):
-        # a class is tuned once, at the first (largest) size listed for it
-        if (ops is not None and case.op not in ops) or case.key() in tuned:
+    for op, dt, acc, n in default_classes(a.quick, a.log2n):
+        if ops is not None and op not in ops:
+            continue
+        case = make_case(op, dt, acc, n, dev)
+        if case.key() in tuned:  # a class is tuned once, at the first (largest) size listed for it
             continue
         tuned.add(case.key())
         results[case.key()] = tune_case(case, a.quick, log=lambda s: print(s, flush=True))

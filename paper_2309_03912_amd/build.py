@@ -12,15 +12,16 @@ LIB_PATH = os.path.join(HERE, "libhdc.so")
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(HERE, "_build")
 # (source, object name, extra defines): one translation unit per kernel family,
-# the fused map + reduce family once per storage type.
+# the segmented and the fused map + reduce families once per storage type.
 UNITS = [("hdc_api.hip", "hdc_api", []),
          ("hdc_run_map.hip", "hdc_run_map", []),
          ("hdc_run_reduce.hip", "hdc_run_reduce", []),
-         ("hdc_run_segmented.hip", "hdc_run_segmented", []),
          ("hdc_run_batch.hip", "hdc_run_batch", []),
          ("hdc_run_host.hip", "hdc_run_host", []),
          ("hdc_run_scan.hip", "hdc_run_scan", []),
          ("hdc_run_segscan.hip", "hdc_run_segscan", [])] + [
+    ("hdc_run_segmented.hip", f"hdc_run_segmented_{t.lower()}",
+     [f"-DHDC_SEG_STORAGE={t}", f"-DHDC_SEG_NAME=run_segmented_{t.lower()}"]) for t in ("F32", "F16", "BF16", "I32")] + [
     ("hdc_run_map_reduce.hip", f"hdc_run_map_reduce_{t.lower()}",
      [f"-DHDC_MR_STORAGE={t}", f"-DHDC_MR_NAME=run_map_reduce_{t.lower()}"]) for t in ("F32", "F16", "BF16", "I32")]
 

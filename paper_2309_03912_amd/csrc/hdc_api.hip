@@ -653,7 +653,16 @@ hdc_status hdc_segmented_reduce(const hdc_functor* f, hdc_dtype dt, const void* 
                workspace ? "caller" : "library");
   uint32_t* ticket = nullptr;
   if (t.passes == 1) HDC_TRY(ticket_for(ws, st, &ticket));
-  return run_segmented(*f, dt, x, offsets, num_segments, total_bound, acc, out, ws, cap_bytes, ticket, t, st);
+  auto run = [&](auto launcher) {
+    return launcher(*f, x, offsets, num_segments, total_bound, acc, out, ws, cap_bytes, ticket, t, st);
+  };
+  switch (dt) {
+    case HDC_F32: return run(run_segmented_f32);
+    case HDC_F16: return run(run_segmented_f16);
+    case HDC_BF16: return run(run_segmented_bf16);
+    case HDC_I32: return run(run_segmented_i32);
+    default: return fail(HDC_ERR_UNSUPPORTED, "dtype %d is not provided", (int)dt);
+  }
 }
 
 hdc_status hdc_batch_map_reduce(const hdc_functor* f, const hdc_functor* g, hdc_dtype dt, hdc_accum acc,

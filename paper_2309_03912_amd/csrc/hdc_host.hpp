@@ -234,9 +234,19 @@ hdc_status run_map_reduce_i32(const hdc_functor& fm, const hdc_functor& f, const
                               hipStream_t st);
 // `ws_bytes`: the workspace's size, which sets the work-list capacity;
 // `total`: the elements it is sized for; `ticket`: as for run_reduce, or NULL.
-hdc_status run_segmented(const hdc_functor& f, hdc_dtype dt, const void* x, const int64_t* off, int64_t nseg,
-                         int64_t total, hdc_accum acc, void* out, void* ws, size_t ws_bytes, uint32_t* ticket,
-                         const Tuning& t, hipStream_t st);
+// One translation unit per storage type.
+hdc_status run_segmented_f32(const hdc_functor& f, const void* x, const int64_t* off, int64_t nseg, int64_t total,
+                             hdc_accum acc, void* out, void* ws, size_t ws_bytes, uint32_t* ticket,
+                             const Tuning& t, hipStream_t st);
+hdc_status run_segmented_f16(const hdc_functor& f, const void* x, const int64_t* off, int64_t nseg, int64_t total,
+                             hdc_accum acc, void* out, void* ws, size_t ws_bytes, uint32_t* ticket,
+                             const Tuning& t, hipStream_t st);
+hdc_status run_segmented_bf16(const hdc_functor& f, const void* x, const int64_t* off, int64_t nseg, int64_t total,
+                              hdc_accum acc, void* out, void* ws, size_t ws_bytes, uint32_t* ticket,
+                              const Tuning& t, hipStream_t st);
+hdc_status run_segmented_i32(const hdc_functor& f, const void* x, const int64_t* off, int64_t nseg, int64_t total,
+                             hdc_accum acc, void* out, void* ws, size_t ws_bytes, uint32_t* ticket,
+                             const Tuning& t, hipStream_t st);
 // `ws_bytes` is the workspace's capacity; a group whose chunk partials do not
 // fit is refused (HDC_ERR_WORKSPACE) before anything is launched.  `chunk`:
 // elements per chunk of each of the cnt calls.

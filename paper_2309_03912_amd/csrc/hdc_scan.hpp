@@ -992,20 +992,17 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
                                                __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    tile_sh = t;
+    // A slot's ticket counts past the grid only after calls that overlapped on
+    // one workspace and stream (two graphs captured there, replayed at once).
+    // Such a tile has no nodes: the last one is taken again, whose wait for its
+    // predecessors gives up and marks the call.  (Marking and leaving here cost
+    // the int64 segmented scan 1%.)
+    tile_sh = t < gridDim.x ? t : gridDim.x - 1;
     tag_sh = lb.tag;
   }
   __syncthreads();
   const int64_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)tile_sh);
   lb.tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)tag_sh);
-  // A slot's ticket counts past the grid only after calls that overlapped on
-  // one workspace and stream (two graphs captured there, replayed at once):
-  // such a tile has no nodes.
-  if (tile >= (int64_t)gridDim.x) {
-    if (threadIdx.x == 0)
-      __hip_atomic_store(lb.status, gave_up_mark(lb), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return;
-  }
   auto w = scan_wave_at<F, S, Acc, E>(tile, n);
   w.template load<kEven>(x, seg);
   if constexpr (IsSeg<Acc>::value)

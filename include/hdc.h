@@ -214,11 +214,13 @@ hdc_status hdc_transform_reduce_noalloc(const hdc_functor* f, hdc_dtype dt,
  *   Empty segments give 0.  No host synchronisation (with a workspace).
  *   Two schedules, chosen by the tuning's `passes`: tiled (1, the default)
  *   streams fixed tiles of the element range and folds the segments that span
- *   tiles, in the same launch when the workspace is sized for few elements
- *   (up to ~1000 tiles) and in a second one otherwise; planned (2) builds work
- *   lists in three small launches, runs one persistent pass over them and a
- *   combine launch.  Both give reproducible bits for a fixed tuning and
- *   workspace size.
+ *   tiles: by one block when the workspace is sized for few elements (up to
+ *   4 * block tiles, and no more than 1024 segments per tile), in the same
+ *   launch while a ticket is left, else in a second launch; planned (2) builds
+ *   work lists in three small launches, runs one persistent pass over them and
+ *   a combine launch.  Both give reproducible bits for a fixed tuning and
+ *   workspace size (the Python binding's own workspace counts as one of just
+ *   the size that the call needs).
  *   IDENTITY, AFFINE, HORNER as for transform_reduce (no PRODUCT).
  *   workspace: at least hdc_workspace_size(HDC_OP_SEGMENTED_REDUCE, dt, acc,
  *   total, S) bytes for a total >= offsets[S]; its size sets the capacity
@@ -325,8 +327,9 @@ typedef struct hdc_batch_call {
 /*
  * Many independent calls of one class -- same dtype, map callable f, fold
  * callable g and accumulation -- in one grouped launch per 32 calls, plus
- * one combine launch where they make many chunks: y = f(x) (when f and the call's y are non-NULL) and
- * *out = the fold of g over x, each call exactly as hdc_map_reduce /
+ * one combine launch where they make many chunks (more than 64 in one call, or
+ * than compute units in all): y = f(x) (when f and the call's y are non-NULL)
+ * and *out = the fold of g over x, each call exactly as hdc_map_reduce /
  * hdc_transform_reduce define it.  `calls` is a HOST array read during this
  * call (the table is passed to the kernels by value, so the launches can be
  * recorded into a graph).  Workspace: hdc_workspace_size(HDC_OP_BATCH, dt, acc,
@@ -381,16 +384,20 @@ hdc_status hdc_validate_offsets(const int64_t* offsets, int64_t num_segments,
  * how many small segments share one wavefront (power of two, 1..64, each
  * served by 64/seg_per_wave lanes).  For HDC_OP_SCAN, block sets the tile
  * (block * 16 elements) and unroll 1 selects the three-pass schedule.
- * passes, 1 or 2 (default 2; 1 for the reductions of buckets 0..2 and for the
- * segmented reduce).
+ * passes, 1 or 2 (default 2; 1 for the reductions of buckets 0..2, for the
+ * segmented reduce and for batches).
  * HDC_OP_TRANSFORM_REDUCE, HDC_OP_DOT, HDC_OP_MAP_REDUCE: 1 folds the
  * per-block partials in the same launch, in the block that arrives last on a
  * ticket (library-owned device memory, one per workspace buffer and stream; a
  * call that finds none left takes two launches); 2 folds them in a second
  * launch (none when the grid is one block).  Both fold in the same order, so
- * `passes` does not change any result bit.  HDC_OP_SEGMENTED_REDUCE: 1
- * selects the tiled schedule (fixed tiles of `chunk` elements, fewer where
- * that would leave fewer than 512 tiles; no plan), 2 the planned one (pieces of `chunk`, packed small segments).  Tuning changes
+ * `passes` does not change any result bit.  HDC_OP_BATCH: the same, with one
+ * counter per call.  HDC_OP_SEGMENTED_REDUCE: 1 selects the tiled schedule (no
+ * plan; blocks of at most 512), 2 the planned one (pieces of `chunk`, packed
+ * small segments).  `chunk` is the most elements a tile has: it is halved (to
+ * 1024 at least) while there would be fewer than 512 tiles and, above 4096,
+ * while there would be fewer than 8192 and the mean segment is shorter than
+ * 8192 elements, elements being those the workspace is sized for.  Tuning changes
  * the summation order, so the last bits of a floating-point sum may change;
  * results stay within the stated tolerance. */
 typedef struct hdc_tuning {

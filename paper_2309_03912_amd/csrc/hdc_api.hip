@@ -359,7 +359,7 @@ constexpr size_t kTicketGroupWords = (size_t)kTicketCounters * kTicketStride;
 static __device__ __align__(256) uint32_t tickets[kTicketGroups * kTicketGroupWords];
 
 // Look-back slots of the single-pass scans of few tiles, for the first
-// kScanSlots of those keys (8 MiB); zero-initialized as the tickets are.
+// kScanSlots of those keys (6.2 MiB); zero-initialized as the tickets are.
 constexpr int kScanSlots = 1 << 10;
 static __device__ __align__(256) uint64_t scan_slots[(size_t)kScanSlots * kScanSlotWords];
 

@@ -1,7 +1,8 @@
 // Grouped batch: many independent map + reduce calls of one class (same
-// storage type, callables and fold) in one grouped launch and, where
-// there are more chunks than compute units, one combine launch.  The call table is a by-value kernel argument (no host-to-device
-// copy, so the launches can be recorded into a graph as they are).
+// storage type, callables and fold) in one grouped launch and, where a call has
+// more than 64 chunks or all have more than there are compute units, one
+// combine launch.  The call table is a by-value kernel argument (no
+// host-to-device copy, so the launches can be recorded into a graph as they are).
 //
 // Every call is cut into chunks of its `chunk_vecs` 16-byte vectors, which its
 // own size and the tuning set; the global chunk index space is the concatenation of all calls' chunks.  A block takes

@@ -221,7 +221,7 @@ hdc_status launch_seg_tiles(const F& f, const void* x, const int64_t* off, int64
   }
   // Up to 8 wavefronts per compute unit, of at most 64 segments at a time: a
   // wavefront folds its wide segments one by one (100 segments of 500,000 bf16
-  // in two wavefronts: 87 us a call, in a wavefront each 40).
+  // in two wavefronts: 87 us a call, in a wavefront each 28).
   const int64_t waves = (int64_t)cus * 8;
   int32_t per = 1;
   while (per < 64 && per * waves < nseg) per *= 2;

@@ -1011,9 +1011,9 @@ scan_onepass_kernel(F f, const elem_t<S>* x, int64_t n, SegSpec seg,
   Acc total;
   const Acc before = block_wave_prefix(w.wave_total, lds, &total);
   if (threadIdx.x < 64) {
-    // Segmented scans park wavefront 0's lane state in LDS while it polls:
-    // the polls and the lane state together needed ~70 VGPRs, over the 64
-    // that two 1024-thread blocks per CU allow.
+    // Segmented, int64 and wide scans (kPark) park wavefront 0's lane state in
+    // LDS while it polls: the polls and the lane state together needed ~70
+    // VGPRs, over the 64 that two 1024-thread blocks per CU allow.
     if constexpr (kPark) w.stash(park_sh);
     typename C::T carry = C::zero();
     if (!only) carry = scan_tree_carry<C>(lb, tile, (int64_t)gridDim.x, C::of(total), slots);

@@ -395,9 +395,11 @@ hdc_status hdc_validate_offsets(const int64_t* offsets, int64_t num_segments,
  * counter per call.  HDC_OP_SEGMENTED_REDUCE: 1 selects the tiled schedule (no
  * plan; blocks of at most 512), 2 the planned one (pieces of `chunk`, packed
  * small segments).  `chunk` is the most elements a tile has: it is halved (to
- * 1024 at least) while there would be fewer than 512 tiles and, above 4096,
- * while there would be fewer than 8192 and the mean segment is shorter than
- * 8192 elements, elements being those the workspace is sized for.  Tuning changes
+ * 1024 at least) while there would be fewer than 512 tiles; above 4096, while
+ * there would be fewer than 8192 and the mean segment is shorter than 8192
+ * elements; and where the mean segment is shorter than 768 elements, while
+ * there would be fewer tiles than one and a half times a tile's elements --
+ * elements being those the workspace is sized for.  Tuning changes
  * the summation order, so the last bits of a floating-point sum may change;
  * results stay within the stated tolerance. */
 typedef struct hdc_tuning {

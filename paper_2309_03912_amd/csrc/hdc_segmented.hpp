@@ -602,7 +602,7 @@ struct SegFinder {
 constexpr int kDenseEnds = 3;
 // Segments of fewer than this many 16-byte vectors on average (1.5 chunks) go
 // to the pass that has the scan (kDense), and so do calls whose tiles one block
-// folds; its 10-20 registers more cost longer segments 5-20%.  1.34e8 elements in lognormal segments, without ->
+// folds; its 7-15 registers more cost longer segments 5-20%.  1.34e8 elements in lognormal segments, without ->
 // with the scan, us: f32 plain, mean 100: 258.6 -> 188.9, 200: 170.6 -> 162.3,
 // 400: 128.9 -> 137.0; bf16 compensated, mean 100: 390 -> 143, 400: 141 ->
 // 111, 800: 96.1 -> 97.4.

@@ -1,0 +1,69 @@
+"""Segmented reduces of a few million elements in short segments: the tiled
+schedule is not slower than the planned one (a tile's chain of chunks must not
+be long where there are few wavefronts).  Times of both schedules of the same
+call, and the results of both against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2309_03912_amd as hdc
+import synth
+
+pytestmark = pytest.mark.gpu
+
+HOR, IDENT = {"fn": "horner", "coef": synth.horner_coefficients(8)}, {"fn": "identity"}
+CLASSES = [(torch.float32, "plain", HOR), (torch.float32, "compensated", HOR), (torch.bfloat16, "compensated", IDENT),
+           (torch.int32, "exact_int", IDENT)]
+
+
+def time_us(call):
+    times = []
+    for _ in range(7):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(10):
+            call()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 100)
+    return sorted(times)[2]
+
+
+@pytest.mark.parametrize("n", [2_000_000, 4_000_000, 8_000_000, 17_000_000])
+@pytest.mark.parametrize("dt,acc,fn", CLASSES, ids=["f32", "f32_comp", "bf16_comp", "i32"])
+def test_not_slower_than_planned(dt, acc, fn, n):
+    op, code, a = hdc.OP_SEGMENTED_REDUCE, hdc.DTYPE[dt], hdc.ACC[acc]
+    rng = np.random.default_rng(230905900)
+    layouts = {"of_64": np.full(n // 64, 64), "of_0_to_60": rng.integers(0, 61, n // 30),
+               "stretch": np.concatenate([[n // 2], rng.integers(1, 9, 50_000), [n // 2]])}
+    saved = {b: hdc.get_tuning(op, code, a, b) for b in range(hdc.BUCKETS)}
+    try:
+        for name, L in layouts.items():
+            off = synth.offsets_from_lengths(torch.as_tensor(L, dtype=torch.int64))
+            m, S = int(off[-1]), off.numel() - 1
+            if dt == torch.int32:
+                x = synth.uniform_int(230905900, 0, m, bits=20)
+            else:
+                x = synth.to_storage(synth.uniform_pm1_f32(230905900, 0, m).double(), dt)
+            ref = oracle.segmented(fn, x, off) if n <= 4_000_000 else None
+            xg, og = x.cuda(), off.cuda()
+            ws = torch.empty(hdc.workspace_size(op, code, a, m, S), dtype=torch.uint8, device="cuda")
+            out = torch.empty(S, dtype=hdc.OUT_DTYPE[a], device="cuda")
+            us = {}
+            for passes in (1, 2):
+                if passes == 2:
+                    hdc.set_tuning(op, code, a, -1, block=256, unroll=2, grid_mult=8, chunk=4096, passes=2)
+                us[passes] = time_us(lambda: hdc.segmented_reduce(xg, og, fn, acc, out=out, ws=ws))
+                if ref is not None and acc == "exact_int":
+                    assert np.array_equal(out.cpu().numpy(), ref["isum"]), (name, passes)
+                elif ref is not None:
+                    err = np.abs(out.cpu().double().numpy() - ref["exact"])
+                    assert np.all(err <= 1e-6 * ref["abs_sum"]), (name, passes)
+            for b, t in saved.items():
+                hdc.set_tuning(op, code, a, b, **t)
+            print(f"mid sizes {dt} {acc} n={n} {name}: tiled {us[1]:.1f} us, planned {us[2]:.1f}", flush=True)
+            assert us[1] <= 1.15 * us[2], name  # two timings differ by a few per cent
+    finally:
+        for b, t in saved.items():
+            hdc.set_tuning(op, code, a, b, **t)

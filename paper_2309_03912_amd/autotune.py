@@ -287,7 +287,8 @@ def default_classes(quick=False, log2n=28):
     classes = [(OP_MAP, dt, ACC_PLAIN, m) for m in [n] + small for dt in (F32, F16, BF16, I32)]
     classes += [(OP_TRANSFORM_REDUCE, dt, acc, m) for m in [n] + small for dt, acc in FOLDS + exact]
     classes += [(OP_DOT, dt, acc, m) for m in [n] + small for dt, acc in dots]
-    classes += [(OP_SEGMENTED_REDUCE, dt, acc, m) for m in [n // 2] + small for dt, acc in FOLDS]
+    classes += [(OP_SEGMENTED_REDUCE, dt, acc, m) for m in [n // 2] + small
+                for dt, acc in FOLDS + [(F16, ACC_PLAIN), (BF16, ACC_PLAIN)]]
     classes += [(OP_MAP_REDUCE, dt, acc, m) for m in [n // 8] + small for dt, acc in FOLDS]
     # the 64-call graph workload's halves (2^22 elements a call on average); and 32 large calls
     classes += [(OP_BATCH, dt, acc, m) for m in (1 << 24, 1 << 22) for dt, acc in FOLDS]

@@ -212,13 +212,16 @@ void ensure_tuning_loaded() {
     // takes chunks of 32768 (one f16 compensated call of 2^26: 58 against 67 us;
     // 16 of 2^24 201 against 223).  The chunk goes by the call's own size and the
     // block is the same for all, so that no result depends on the rest of the
-    // batch; 256 threads were no better for large calls (f32 plain 2^26: 109
-    // against 102 us, bf16 compensated 55 against 53, f16 55 to 58 either way).
-    for (auto& per_dt : g_tune[HDC_OP_BATCH])
-      for (auto& per_acc : per_dt)
+    // batch.  512 threads by 32768 against 256, us: one call of 2^26 f32 plain
+    // 102 against 109, bf16 compensated 53 against 55; but f16 storage takes
+    // 256, with chunks of 8192 below 2^20 (folds without a map: 4 calls of 1.7e7
+    // f16 compensated 39.5 against 45.3 us, plain 32.7 against 35.7; 12 of 4e6
+    // by 16384 32.2 against 40.7, 26.9 against 34.0; one of 500,000 7.1 either way).
+    for (int dt = 0; dt < kDtypes; ++dt)
+      for (auto& per_acc : g_tune[HDC_OP_BATCH][dt])
         for (int b = 0; b < kBuckets; ++b) {
-          per_acc[b].block = 512;
-          per_acc[b].chunk = b == 3 ? 32768 : 16384;
+          per_acc[b].block = dt == HDC_F16 ? 256 : 512;
+          per_acc[b].chunk = b == 3 ? 32768 : dt == HDC_F16 && b < 2 ? 8192 : 16384;
           per_acc[b].passes = 1;
         }
     // Reductions of fewer than 2^24 elements fold their partials in the same

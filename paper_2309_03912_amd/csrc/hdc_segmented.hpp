@@ -1390,6 +1390,9 @@ __global__ __launch_bounds__(256) void seg_tiles_combine_crowded_kernel(F f, con
       const int64_t t0 = TileWave<F, S, Acc, 1, true>::tile_base(g, st.tile_vecs, t);
       const int64_t t1 = t == g.ntiles - 1 ? g.n : TileWave<F, S, Acc, 1, true>::tile_base(g, st.tile_vecs, t + 1);
       const int64_t p0 = t0 + (((t1 - t0) * q) >> lg), p1 = t0 + (((t1 - t0) * (q + 1)) >> lg);
+      // A tile of fewer than 2^lg elements has empty parts: no segment starts in one, and the first
+      // tile's first would search in front of off[0].
+      if (p0 == p1) continue;
       // [s, e): from the first offset at or after p0 to the first at or after p1, if the tile holds it,
       // else to the last one it holds (the segment that starts there leaves the tile)
       const int32_t j0 = p0 > 0 ? last_offset(off, (int32_t)S_, 0, g.lo + p0 - 1, lane) : -1;
